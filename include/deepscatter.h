@@ -461,7 +461,9 @@ ds_status ds_cloud_majorant(const ds_cloud *cloud, float *majorant);
  * of record i uses stream id i * 2^20 + s.  Records with an unusable direction
  * get 0.  In DS_LIGHT_DIRECTIONAL mode light_dir is omega_l per record; in
  * DS_LIGHT_ENVIRONMENT mode it is ignored but must still be a valid pointer.
- * 1 <= spp <= 2^20, P < 2^40.  Library-owned workspace: 16 * P * ceil(spp/64) bytes. */
+ * 1 <= spp <= 2^20, P < 2^40.  Library-owned workspace: 16 * P * ceil(spp/64) bytes, and
+ * for the paths of one launch (at most 2^23, or one record's) 8 bytes each plus 4 bytes per
+ * record (at most 2^23). */
 ds_status ds_trace_li(ds_ctx *ctx, const ds_cloud *cloud, const ds_tracer_params *params,
                       const float *pos, const float *view_dir, const float *light_dir, int64_t P,
                       int spp, uint64_t seed, double *mean_out, double *var_out);
@@ -488,7 +490,8 @@ typedef struct ds_adaptive {
  * order and the paths past a record's stopping batch are discarded, so estimates and path
  * counts are those of one batch per round.  Synchronises once per round.  Library-owned
  * workspace: 16 * P * ceil(batch_spp / 64) * k + 17 * P bytes, k the largest round (1 if
- * batch_spp is not a multiple of 64; its partial sums are kept within 256 MiB). */
+ * batch_spp is not a multiple of 64; its partial sums are kept within 256 MiB), and the
+ * launch's as ds_trace_li. */
 ds_status ds_trace_li_adaptive(ds_ctx *ctx, const ds_cloud *cloud, const ds_tracer_params *params,
                                const ds_adaptive *adaptive, const float *pos,
                                const float *view_dir, const float *light_dir, int64_t P,

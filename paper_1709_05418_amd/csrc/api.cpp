@@ -2079,7 +2079,7 @@ ds_status ds_trace_li(ds_ctx *ctx, const ds_cloud *cloud, const ds_tracer_params
     if (st || P == 0)
         return st;
     DS_HIP(hipSetDevice(ctx->device));
-    st = ensure_ws(ctx, sizeof(double) * 2 * (size_t)P * tracer_blocks(spp));
+    st = ensure_ws(ctx, sizeof(double) * 2 * (size_t)P * tracer_blocks(spp) + tracer_ws(P, spp));
     if (st)
         return st;
     return tracer_li(ctx->stream, cloud, tp, pos, view_dir, light_dir, P, spp, seed,
@@ -2094,7 +2094,7 @@ static ds_status adaptive_li(ds_ctx *ctx, const ds_cloud *cloud, const TracerPar
 {
     const int ahead = tracer_adaptive_ahead(P, ad->batch_spp, ad->max_spp);
     ds_status st = ensure_ws(ctx, sizeof(double) * 2 * (size_t)P * tracer_blocks(ad->batch_spp) *
-                                      (size_t)ahead);
+                                      (size_t)ahead + tracer_ws(P, ad->batch_spp * ahead));
     if (st)
         return st;
     uint8_t *active = cv.take<uint8_t>((size_t)P);
@@ -2163,7 +2163,7 @@ ds_status ds_render_mc(ds_ctx *ctx, const ds_cloud *cloud, const ds_tracer_param
     if (N == 0)
         return DS_OK;
     DS_HIP(hipSetDevice(ctx->device));
-    st = ensure_ws(ctx, sizeof(double) * 2 * (size_t)N * tracer_blocks(spp));
+    st = ensure_ws(ctx, sizeof(double) * 2 * (size_t)N * tracer_blocks(spp) + tracer_ws(N, spp));
     if (st)
         return st;
     return tracer_render(ctx->stream, cloud, tp, light_dir, ray_o, ray_d, N, spp, seed,
@@ -2239,7 +2239,7 @@ static ds_status make_records(ds_ctx *ctx, const ds_cloud *cloud, const ds_trace
         st = adaptive_li(ctx, cloud, tp, ad, p, v, l, N, derived_key(seed, 0), cv, m, li_var,
                          spp_out);
     } else {
-        st = ensure_ws(ctx, sizeof(double) * 2 * (size_t)N * tracer_blocks(spp));
+        st = ensure_ws(ctx, sizeof(double) * 2 * (size_t)N * tracer_blocks(spp) + tracer_ws(N, spp));
         if (st)
             return st;
         st = tracer_li(s, cloud, tp, p, v, l, N, spp, derived_key(seed, 0),
@@ -2337,7 +2337,8 @@ ds_status ds_render_rpnn(ds_ctx *ctx, const ds_cloud *cloud, const ds_net *net,
             return st;
         const double *mc = nullptr;
         if (fallback_spp > 0) {
-            st = ensure_ws(ctx, sizeof(double) * 2 * n * tracer_blocks(fallback_spp));
+            st = ensure_ws(ctx, sizeof(double) * 2 * n * tracer_blocks(fallback_spp) +
+                                     tracer_ws(N, fallback_spp));
             if (st)
                 return st;
             st = tracer_li(s, cloud, tp, pos, view, light, N, fallback_spp,
@@ -2576,7 +2577,7 @@ ds_status ds_render_mc_lights(ds_ctx *ctx, const ds_cloud *cloud, const ds_trace
     if (N == 0)
         return DS_OK;
     DS_HIP(hipSetDevice(ctx->device));
-    st = ensure_ws(ctx, sizeof(double) * 2 * (size_t)N * tracer_blocks(spp));
+    st = ensure_ws(ctx, sizeof(double) * 2 * (size_t)N * tracer_blocks(spp) + tracer_ws(N, spp));
     if (st)
         return st;
     const float unused[3] = {0.f, 0.f, 1.f};
@@ -2674,7 +2675,8 @@ ds_status ds_render_rpnn_lights(ds_ctx *ctx, const ds_cloud *cloud, const ds_net
             return st;
         const double *mc = nullptr;
         if (fallback_spp > 0) {
-            st = ensure_ws(ctx, sizeof(double) * 2 * r * tracer_blocks(fallback_spp));
+            st = ensure_ws(ctx, sizeof(double) * 2 * r * tracer_blocks(fallback_spp) +
+                                     tracer_ws(R, fallback_spp));
             if (st)
                 return st;
             st = tracer_li(s, cloud, dir_tp, pos, view, light, R, fallback_spp,

@@ -83,7 +83,8 @@ struct ds_cloud {
     void *tables = nullptr;    // device: GatherLevel[K] then FusedLevel[K]
     float *mu = nullptr;       // extinction sigma_max * d on the base grid (tracer medium)
     // the same extinction corner-packed (8 float32 corners, 32 bytes per cell, zero border),
-    // built on the cloud's first tracer call; the tracer reads one cell per lookup
+    // then the bits of the occupied bricks, built on the cloud's first tracer call; the
+    // tracer reads one cell per lookup
     mutable float4 *mu_cells = nullptr;
     float majorant = 0.f;      // sigma_max * max(d)
 };
@@ -327,6 +328,9 @@ struct TracerParams {
 bool unit_host(const float *v, float *u);  // normalise a host 3-vector; false if unusable
 ds_status tracer_prepare(ds_cloud *c, const void *density, ds_dtype dt);
 int tracer_blocks(int spp);  // partial sums per record
+// Bytes the path walker needs behind the partial sums of P records with spp paths each (the
+// active records of a launch and its path values)
+size_t tracer_ws(int64_t P, int spp);
 // mask: when not NULL, only records with (mask[i] & mask_bits) == mask_bits are traced
 // (the others get 0)
 ds_status tracer_li(hipStream_t s, const ds_cloud *c, const TracerParams &tp, const float *pos,
@@ -337,7 +341,7 @@ ds_status tracer_li(hipStream_t s, const ds_cloud *c, const TracerParams &tp, co
 // zq * sqrt(var of mean) <= rel * |mean| or max_spp (a multiple of batch) paths; a round
 // traces up to `ahead` batches of the records still running (tracer_adaptive_ahead) and
 // checks the rule after each in order.  Workspace: partial (2 * P * tracer_blocks(batch) *
-// ahead doubles), active (P bytes), sums (2 P doubles), left (one counter).  Synchronises
+// ahead doubles, then tracer_ws(P, batch * ahead) bytes), active (P bytes), sums (2 P doubles), left (one counter).  Synchronises
 // once per round; rounds (may be NULL) gets the round count.
 ds_status tracer_li_adaptive(hipStream_t s, const ds_cloud *c, const TracerParams &tp,
                              const float *pos, const float *view, const float *light, int64_t P,
