@@ -47,6 +47,60 @@ bool unit_host(const float *v, float *u)
     return true;
 }
 
+void blocks_free(ds_ctx *ctx)
+{
+    std::lock_guard<std::mutex> lock(ctx->blocks_mutex);
+    for (auto &b : ctx->blocks)
+        (void)hipFree(b.first);
+    ctx->blocks.clear();
+    ctx->blocks_bytes = 0;
+}
+
+void *block_take(ds_ctx *ctx, size_t *bytes)
+{
+    {
+        std::lock_guard<std::mutex> lock(ctx->blocks_mutex);
+        size_t best = ctx->blocks.size();
+        for (size_t i = 0; i < ctx->blocks.size(); ++i) {
+            const size_t b = ctx->blocks[i].second;
+            if (b >= *bytes && b - *bytes <= *bytes / 4 &&
+                (best == ctx->blocks.size() || b < ctx->blocks[best].second))
+                best = i;
+        }
+        if (best < ctx->blocks.size()) {
+            void *p = ctx->blocks[best].first;
+            *bytes = ctx->blocks[best].second;
+            ctx->blocks_bytes -= *bytes;
+            ctx->blocks.erase(ctx->blocks.begin() + best);
+            return p;
+        }
+    }
+    void *p = nullptr;
+    if (hipMalloc(&p, *bytes) == hipSuccess)
+        return p;
+    (void)hipGetLastError();
+    blocks_free(ctx);
+    return hipMalloc(&p, *bytes) == hipSuccess ? p : nullptr;
+}
+
+void block_give(ds_ctx *ctx, void *p, size_t bytes)
+{
+    if (!p)
+        return;
+    if (ctx) {
+        std::lock_guard<std::mutex> lock(ctx->blocks_mutex);
+        if (ctx->blocks_bytes + bytes <= kBlocksKept) {
+            try {
+                ctx->blocks.emplace_back(p, bytes);
+                ctx->blocks_bytes += bytes;
+                return;
+            } catch (...) {
+            }
+        }
+    }
+    (void)hipFree(p);
+}
+
 namespace {
 
 int level_dim(int n, int i)
@@ -169,9 +223,9 @@ ds_status gather_cells(ds_ctx *ctx, const ds_cloud *c)
 {
     if (c->cells32)
         return DS_OK;
-    float4 *cells = nullptr;
-    DS_CHECK(hipMalloc(&cells, sizeof(float4) * 2 * (size_t)c->n_cells32) == hipSuccess,
-             DS_ERR_OOM, "out of device memory for the float32 corner cells (%lld cells of 32 bytes)",
+    size_t bytes = sizeof(float4) * 2 * (size_t)c->n_cells32;
+    float4 *cells = static_cast<float4 *>(block_take(c->ctx, &bytes));
+    DS_CHECK(cells, DS_ERR_OOM, "out of device memory for the float32 corner cells (%lld cells of 32 bytes)",
              (long long)c->n_cells32);
     ds_status st = cloud_pack32(ctx->stream, c->pyr, c->L, c->lv, cells);
     std::vector<GatherLevel> gl((size_t)c->K);
@@ -191,6 +245,7 @@ ds_status gather_cells(ds_ctx *ctx, const ds_cloud *c)
         (void)hipFree(cells);
         return st;
     }
+    c->cells32_bytes = bytes;
     c->cells32 = cells;
     return DS_OK;
 }
@@ -810,6 +865,7 @@ ds_status ds_destroy(ds_ctx *ctx)
     (void)hipFree(ctx->ws);
     (void)hipFree(ctx->ws2);
     (void)hipFree(ctx->truncated);
+    blocks_free(ctx);
     delete ctx;
     return DS_OK;
 }
@@ -840,17 +896,31 @@ ds_status ds_cloud_create(ds_ctx *ctx, const void *density_dev, ds_dtype dtype, 
                      n_levels);
     DS_HIP(hipSetDevice(ctx->device));
     const int64_t nvox = (int64_t)nx * ny * nz;
-    double sum = 0.0;
-    int64_t count = 0;
-    ds_status st = cloud_mean(ctx->stream, density_dev, dtype, nvox, &sum, &count);
-    if (st)
-        return st;
-    DS_CHECK(count > 0 && sum > 0.0, DS_ERR_INVALID_ARG,
-             "ds_cloud_create: the density grid has no positive voxel");
-
     ds_cloud *c = new (std::nothrow) ds_cloud();
     DS_CHECK(c, DS_ERR_OOM, "ds_cloud_create: out of host memory");
+    void *scratch = nullptr;
     c->ctx = ctx;
+    auto fail = [&](ds_status s) {
+        (void)hipStreamSynchronize(ctx->stream);
+        (void)hipFree(scratch);
+        ds_cloud_destroy(c);
+        return s;
+    };
+    if (hipMalloc(&scratch, cloud_scratch_bytes(n_levels)) != hipSuccess) {
+        set_error("ds_cloud_create: out of device memory for the build's scratch");
+        return fail(DS_ERR_OOM);
+    }
+    DensityScan scan;
+    ds_status st = cloud_scan(ctx->stream, density_dev, dtype, nvox, sigma_max, scratch, &scan);
+    if (st)
+        return fail(st);
+    const double sum = (double)scan.hi + (double)scan.lo;
+    const int64_t count = (int64_t)scan.count;
+    if (!(count > 0 && sum > 0.0)) {
+        set_error("ds_cloud_create: the density grid has no positive voxel");
+        return fail(DS_ERR_INVALID_ARG);
+    }
+    c->majorant = scan.max;
     c->nx = nx;
     c->ny = ny;
     c->nz = nz;
@@ -914,28 +984,27 @@ ds_status ds_cloud_create(ds_ctx *ctx, const void *density_dev, ds_dtype dtype, 
         coff += (int64_t)(l.nx + 2 * bd) * (l.ny + 2 * bd) * (l.nz + 2 * bd);
     }
     c->n_cells = coff;
-    auto fail = [&](ds_status s) {
-        ds_cloud_destroy(c);
-        return s;
-    };
-    if (hipMalloc(&c->pyr, sizeof(float) * c->pyr_elems) != hipSuccess) {
-        set_error("ds_cloud_create: out of device memory for the float32 pyramid (%lld floats)",
-                  (long long)c->pyr_elems);
+    auto up = [](size_t b) { return (b + 255) / 256 * 256; };
+    const int64_t volumes = cloud_volume_floats(ny, nz, n_levels, c->lv);
+    const size_t cell_b = up(std::max(sizeof(uint4) * (size_t)c->n_cells,
+                                      sizeof(float) * (size_t)volumes));
+    const size_t pyr_b = up(sizeof(float) * (size_t)c->pyr_elems);
+    c->block_bytes = cell_b + pyr_b + sizeof(float) * (size_t)nvox;
+    c->block = block_take(ctx, &c->block_bytes);
+    if (!c->block) {
+        set_error("ds_cloud_create: out of device memory for the pyramid and its packed copy "
+                  "(%lld floats, %lld cells)", (long long)c->pyr_elems, (long long)c->n_cells);
         return fail(DS_ERR_OOM);
     }
-    if (hipMalloc(&c->cells, sizeof(uint4) * c->n_cells) != hipSuccess) {
-        set_error("ds_cloud_create: out of device memory for the packed pyramid (%lld cells)",
-                  (long long)c->n_cells);
-        return fail(DS_ERR_OOM);
-    }
+    c->cells = static_cast<uint4 *>(c->block);
+    c->pyr = reinterpret_cast<float *>(static_cast<char *>(c->block) + cell_b);
+    c->mu = reinterpret_cast<float *>(static_cast<char *>(c->block) + cell_b + pyr_b);
     float scale = (float)((double)sigma_max / c->mean);
-    st = cloud_pyramid(ctx->stream, density_dev, dtype, nx, ny, nz, scale, n_levels, c->lv, c->pyr);
+    st = cloud_pyramid(ctx->stream, density_dev, dtype, nx, ny, nz, scale, sigma_max, n_levels, c->lv,
+                       c->pyr, c->mu, scratch, reinterpret_cast<float *>(c->cells));
     if (st)
         return fail(st);
     st = cloud_pack(ctx->stream, c->pyr, n_levels, c->lv, c->cells);
-    if (st)
-        return fail(st);
-    st = tracer_prepare(c, density_dev, dtype);
     if (st)
         return fail(st);
     // device-side per-stencil-level tables
@@ -978,6 +1047,7 @@ ds_status ds_cloud_create(ds_ctx *ctx, const void *density_dev, ds_dtype dtype, 
         e = hipStreamSynchronize(ctx->stream);
     if (e != hipSuccess)
         return fail(hip_fail(e, "ds_cloud_create"));
+    (void)hipFree(scratch);
     *out = c;
     return DS_OK;
 }
@@ -1062,14 +1132,19 @@ ds_status ds_cloud_destroy(ds_cloud *c)
 {
     if (!c)
         return DS_OK;
-    if (c->ctx)
-        (void)hipStreamSynchronize(c->ctx->stream);
-    (void)hipFree(c->pyr);
-    (void)hipFree(c->cells32);
-    (void)hipFree(c->mu_cells);
-    (void)hipFree(c->cells);
+    // the blocks may go to another cloud: wait for every stream that may still read them, as
+    // freeing them does
+    int dev = -1;
+    (void)hipGetDevice(&dev);
+    (void)hipSetDevice(c->ctx->device);
+    (void)hipStreamSynchronize(c->ctx->stream);
+    (void)hipDeviceSynchronize();
+    if (dev >= 0)
+        (void)hipSetDevice(dev);
+    block_give(c->ctx, c->block, c->block_bytes);
+    block_give(c->ctx, c->cells32, c->cells32_bytes);
+    block_give(c->ctx, c->mu_cells, c->mu_cells_bytes);
     (void)hipFree(c->tables);
-    (void)hipFree(c->mu);
     delete c;
     return DS_OK;
 }

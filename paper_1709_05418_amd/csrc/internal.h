@@ -5,7 +5,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <mutex>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/deepscatter.h"
@@ -59,6 +61,10 @@ struct ds_ctx {
     size_t ws2_bytes = 0;
     // device: paths of the tracer calls stopped at the bound on tentative collisions
     unsigned long long *truncated = nullptr;
+    // device blocks of destroyed clouds, kept for the next ones (see block_take)
+    std::mutex blocks_mutex;
+    std::vector<std::pair<void *, size_t>> blocks;
+    size_t blocks_bytes = 0;
 };
 
 struct ds_cloud {
@@ -72,6 +78,11 @@ struct ds_cloud {
     ds::Level lv[ds::kMaxLevels];
     int K = 0;
     int mips[ds::kMaxK];
+    // one allocation: the packed FP16 levels (cells), the float32 levels (pyr), the extinction
+    // (mu); while the cloud is built the cells hold its partly filtered volumes
+    void *block = nullptr;
+    size_t block_bytes = 0;
+    mutable size_t cells32_bytes = 0, mu_cells_bytes = 0;  // as allocated (block_take)
     float *pyr = nullptr;      // float32 levels, concatenated
     int64_t pyr_elems = 0;
     // corner-packed float32 levels for the plain gather (8 corners, 32 bytes per cell), built
@@ -150,12 +161,35 @@ struct ds_adam {
 
 namespace ds {
 
+// Device memory of the clouds.  Freeing and allocating hundreds of MB for every cloud costs
+// 0.25 ms a block at best, and 5 to 20 ms, now and then a second, once the driver has to
+// wipe and remap them (measured over 300 loads of a 256^3 cloud), so a context keeps up to
+// kBlocksKept bytes of its destroyed clouds' blocks and hands them to the next clouds.
+// block_take: a kept block of *bytes .. 1.25 *bytes, else a new one (the kept ones are
+// given back first where memory runs out); *bytes becomes its size; NULL if out of memory.
+// block_give: the caller has synchronised the device.  Safe from several threads.
+constexpr size_t kBlocksKept = size_t(4) << 30;
+void *block_take(ds_ctx *ctx, size_t *bytes);
+void block_give(ds_ctx *ctx, void *p, size_t bytes);
+void blocks_free(ds_ctx *ctx);
+
 // ------------------------------------------------------------------ kernels (launchers)
 // cloud.hip
-ds_status cloud_mean(hipStream_t s, const void *d, ds_dtype dt, int64_t n, double *sum,
-                     int64_t *count);
+// Sum (hi + lo) and count of d over d > 0, and the largest extinction sigma d
+struct DensityScan {
+    float hi, lo, max;
+    unsigned long long count;
+};
+// bytes of the scratch a cloud of L levels is built in
+size_t cloud_scratch_bytes(int L);
+// one pass over the density: the scan (copied to *host; synchronises)
+ds_status cloud_scan(hipStream_t s, const void *d, ds_dtype dt, int64_t n, float sigma,
+                     void *scratch, DensityScan *host);
+// every level, and mu = sigma d; volumes: cloud_volume_floats() floats
+int64_t cloud_volume_floats(int ny, int nz, int L, const Level *lv);
 ds_status cloud_pyramid(hipStream_t s, const void *d, ds_dtype dt, int nx, int ny, int nz,
-                        float scale, int L, const Level *lv, float *pyr);
+                        float scale, float sigma, int L, const Level *lv, float *pyr, float *mu,
+                        void *scratch, float *volumes);
 ds_status cloud_pack(hipStream_t s, const float *pyr, int L, const Level *lv, uint4 *cells);
 ds_status cloud_pack32(hipStream_t s, const float *pyr, int L, const Level *lv, float4 *cells);
 
@@ -326,7 +360,6 @@ struct TracerParams {
     int set_m = 0;
 };
 bool unit_host(const float *v, float *u);  // normalise a host 3-vector; false if unusable
-ds_status tracer_prepare(ds_cloud *c, const void *density, ds_dtype dt);
 int tracer_blocks(int spp);  // partial sums per record
 // Bytes the path walker needs behind the partial sums of P records with spp paths each (the
 // active records of a launch and its path values)

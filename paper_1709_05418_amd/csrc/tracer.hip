@@ -1081,38 +1081,6 @@ __global__ void __launch_bounds__(256) k_first_hits_set(Medium M, TracerParams t
     hit[i] = h ? 1 : 0;
 }
 
-__global__ void __launch_bounds__(256) k_mu(const void *d, ds_dtype dt, int64_t n, float sigma,
-                                            float *mu)
-{
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        float v;
-        if (dt == DS_F32)
-            v = static_cast<const float *>(d)[i];
-        else
-            v = __uint_as_float((uint32_t) static_cast<const uint16_t *>(d)[i] << 16);
-        mu[i] = sigma * v;
-    }
-}
-
-__global__ void __launch_bounds__(256) k_max(const float *x, int64_t n, float *out)
-{
-    __shared__ float s[256];
-    float m = 0.f;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x)
-        m = fmaxf(m, x[i]);
-    s[threadIdx.x] = m;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w)
-            s[threadIdx.x] = fmaxf(s[threadIdx.x], s[threadIdx.x + w]);
-        __syncthreads();
-    }
-    if (threadIdx.x == 0)
-        out[blockIdx.x] = s[0];
-}
-
 __global__ void __launch_bounds__(256) k_philox(const uint32_t *ck, int64_t n, uint32_t *out)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1256,9 +1224,9 @@ ds_status medium_cells(hipStream_t s, const ds_cloud *c)
     const int64_t n = (int64_t)(c->nx + 2) * (c->ny + 2) * (c->nz + 2);
     const Bricks b = bricks(c);
     const int64_t occ64 = (b.words + 2) / 2;  // 8-byte units, the flag word included
-    float4 *cells = nullptr;
-    DS_CHECK(hipMalloc(&cells, sizeof(float4) * 2 * (size_t)n + 8 * (size_t)occ64) == hipSuccess,
-             DS_ERR_OOM,
+    size_t bytes = sizeof(float4) * 2 * (size_t)n + 8 * (size_t)occ64;
+    float4 *cells = static_cast<float4 *>(block_take(c->ctx, &bytes));
+    DS_CHECK(cells, DS_ERR_OOM,
              "out of device memory for the corner-packed extinction (%lld cells of 32 bytes)",
              (long long)n);
     Level base = {};
@@ -1279,6 +1247,7 @@ ds_status medium_cells(hipStream_t s, const ds_cloud *c)
         (void)hipFree(cells);
         return st;
     }
+    c->mu_cells_bytes = bytes;
     c->mu_cells = cells;
     return DS_OK;
 }
@@ -1469,31 +1438,6 @@ ds_status launch_render_mc(hipStream_t s, const ds_cloud *c, const TracerParams 
 }
 
 }  // namespace
-
-ds_status tracer_prepare(ds_cloud *c, const void *density, ds_dtype dt)
-{
-    const int64_t n = (int64_t)c->nx * c->ny * c->nz;
-    DS_CHECK(hipMalloc(&c->mu, (size_t)n * sizeof(float)) == hipSuccess, DS_ERR_OOM,
-             "out of device memory for the extinction grid");
-    hipStream_t s = c->ctx->stream;
-    int grid = (int)((n + 255) / 256 < 16384 ? (n + 255) / 256 : 16384);
-    k_mu<<<grid, 256, 0, s>>>(density, dt, n, c->sigma_max, c->mu);
-    float *part = nullptr;
-    DS_HIP(hipMalloc(&part, 1024 * sizeof(float)));
-    k_max<<<1024, 256, 0, s>>>(c->mu, n, part);
-    k_max<<<1, 256, 0, s>>>(part, 1024, part);
-    float mx = 0.f;
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(&mx, part, sizeof(float), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess)
-        e = hipStreamSynchronize(s);
-    (void)hipFree(part);
-    if (e != hipSuccess)
-        return hip_fail(e, "majorant");
-    c->majorant = mx;
-    return DS_OK;
-}
 
 size_t tracer_ws(int64_t P, int spp)
 {
