@@ -14,7 +14,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdeepscatter.so")
 ARCH = os.environ.get("DS_OFFLOAD_ARCH", "gfx950")
 
-SOURCES = ["api.cpp", "cloud.hip", "gather.hip", "mlp.hip", "fused.hip", "order.hip", "train.hip",
+SOURCES = ["api.cpp", "cloud.hip", "gather.hip", "chain.hip", "fused.hip", "order.hip", "train.hip",
            "tracer.hip"]
 
 FLAGS = [

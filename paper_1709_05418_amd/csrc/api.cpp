@@ -110,37 +110,6 @@ int level_dim(int n, int i)
     return d < 1 ? 1 : (int)d;
 }
 
-struct ParamOffsets {
-    std::vector<int64_t> V, W1, b1, W2, b2, hw, hb;
-};
-
-ParamOffsets param_offsets(int K, int W, int H)
-{
-    ParamOffsets o;
-    int64_t off = 0;
-    for (int k = 0; k < K; ++k) {
-        o.V.push_back(off);
-        off += (int64_t)W * 226;
-        o.W1.push_back(k ? off : -1);
-        if (k)
-            off += (int64_t)W * W;
-        o.b1.push_back(off);
-        off += W;
-        o.W2.push_back(off);
-        off += (int64_t)W * W;
-        o.b2.push_back(off);
-        off += W;
-    }
-    for (int m = 0; m < H; ++m) {
-        int rows = m == H - 1 ? 1 : W;
-        o.hw.push_back(off);
-        off += (int64_t)rows * W;
-        o.hb.push_back(off);
-        off += rows;
-    }
-    return o;
-}
-
 bool desc_ok(const ds_net_desc *d)
 {
     return d && d->K >= 1 && d->K <= kMaxK && d->W >= 1 && d->W <= 256 && d->H >= 1 && d->H <= 8;
@@ -298,105 +267,24 @@ ds_status forward_plain(ds_ctx *ctx, const ds_net *net, const float *z, int64_t 
 {
     if (net->kind == 1)
         return mlp_forward(ctx, net, z, rows, out, pre, O, F, T);
-    const int K = net->K, W = net->W, H = net->H;
-    const int D = kStencil * K + 1;
-    const float *th = net->theta;
-    ParamOffsets po = param_offsets(K, W, H);
-    for (int64_t r0 = 0; r0 < rows; r0 += kChunk) {
-        int M = (int)((rows - r0) < kChunk ? (rows - r0) : kChunk);
-        const float *zc = z + r0 * D;
-        for (int k = 0; k < K; ++k) {
-            GemmArgs g1 = {};
-            g1.M = M;
-            g1.N = W;
-            g1.A1 = zc + (int64_t)k * kStencil;
-            g1.lda1 = D;
-            g1.K1 = kStencil;
-            g1.B1 = th + po.V[k];
-            g1.ldb1 = 226;
-            if (k > 0) {
-                g1.A2 = O;
-                g1.lda2 = W;
-                g1.K2 = W;
-                g1.B2 = th + po.W1[k];
-                g1.ldb2 = W;
-            }
-            g1.g = zc + (int64_t)kStencil * K;
-            g1.ldg = D;
-            g1.gw = th + po.V[k] + 225;
-            g1.ldgw = 226;
-            g1.bias = th + po.b1[k];
-            g1.C = F;
-            g1.ldc = W;
-            g1.relu = 1;
-            ds_status st = gemm_f32(ctx->stream, g1);
-            if (!st && amax)
-                st = amax_into(ctx->stream, F, (int64_t)M * W, amax + k);
-            if (st)
-                return st;
-            GemmArgs g2 = {};
-            g2.M = M;
-            g2.N = W;
-            g2.A1 = F;
-            g2.lda1 = W;
-            g2.K1 = W;
-            g2.B1 = th + po.W2[k];
-            g2.ldb1 = W;
-            g2.bias = th + po.b2[k];
-            if (k > 0) {
-                g2.R = O;
-                g2.ldr = W;
-            }
-            g2.C = O;
-            g2.ldc = W;
-            g2.relu = 1;
-            st = gemm_f32(ctx->stream, g2);
-            if (!st && amax)
-                st = amax_into(ctx->stream, O, (int64_t)M * W, amax + K);
-            if (st)
-                return st;
-        }
-        const float *in = O;
-        float *bufs[2] = {T, F};
-        for (int m = 0; m < H; ++m) {
-            bool last = m == H - 1;
-            GemmArgs g = {};
-            g.M = M;
-            g.N = last ? 1 : W;
-            g.A1 = in;
-            g.lda1 = W;
-            g.K1 = W;
-            g.B1 = th + po.hw[m];
-            g.ldb1 = W;
-            g.bias = th + po.hb[m];
-            g.C = last ? out + r0 : bufs[m & 1];
-            g.ldc = last ? 1 : W;
-            if (last && pre) {
-                g.pre = pre + r0;
-                g.ldpre = 1;
-            }
-            g.relu = 1;
-            ds_status st = gemm_f32(ctx->stream, g);
-            if (!st && amax && !last)
-                st = amax_into(ctx->stream, bufs[m & 1], (int64_t)M * W, amax + K + 1 + m);
-            if (st)
-                return st;
-            in = bufs[m & 1];
-        }
-    }
-    return DS_OK;
+    ChainArgs a = {};
+    a.z = z;
+    a.theta = net->theta;
+    a.pack = net->chain;
+    a.M = rows;
+    a.K = net->K;
+    a.W = net->W;
+    a.H = net->H;
+    a.out = out;
+    a.pre = pre;
+    a.amax = amax;
+    return chain_forward(ctx->stream, a, false);
 }
 
-// Workspace of one minibatch: per block the first-layer pre-activations H, their
-// ReLU F1, the second-layer pre-activations A and the block outputs O; per
-// trailing layer its pre-activations and outputs; gradient scratch.
-struct TrainWs {
-    float *H, *F1, *A, *O, *HA, *HO, *dcur, *dnext, *dh, *dpre, *sq;
-    float *split;          // split-K partial products (BF16 training)
-    size_t split_floats;
-};
-
-// Training workspace of a minibatch of B samples, in floats (both network kinds).
+// Training workspace of a minibatch of B samples, in floats (both network kinds).  The
+// progressive network's: per block the outputs F1, O of its two layers and their
+// pre-activation gradients DH, DA, the same (HO, DY) per dense trailing layer, and per row
+// d loss / d pre and the squared loss.
 size_t train_ws_floats(const ds_net *net, int B)
 {
     if (net->kind == 1) {
@@ -409,15 +297,13 @@ size_t train_ws_floats(const ds_net *net, int B)
         split = split > csum ? split : csum;
         return 2 * act + 2 * (size_t)B * net->W + 2 * (size_t)B + split;
     }
-    const size_t BW = (size_t)B * net->W, K = net->K, Hh = net->H;
-    const size_t split = (size_t)16 * net->W * 226;
-    return 4 * K * BW + 2 * Hh * BW + 3 * BW + 2 * (size_t)B + split;
+    const size_t BW = (size_t)B * net->W;
+    return 4 * net->K * BW + 2 * (net->H - 1) * BW + 2 * (size_t)B;
 }
 
-ds_status train_ws(ds_net *net, int B, TrainWs &w)
+ds_status train_ws(ds_net *net, int B, ChainArgs &a)
 {
-    const size_t BW = (size_t)B * net->W, K = net->K, Hh = net->H;
-    const size_t split = (size_t)16 * net->W * 226;
+    const size_t BW = (size_t)B * net->W, K = net->K, Hd = net->H - 1;
     const size_t need = train_ws_floats(net, B);
     if (net->tws_floats < need) {
         if (net->tws) {
@@ -430,30 +316,19 @@ ds_status train_ws(ds_net *net, int B, TrainWs &w)
         net->tws_floats = need;
     }
     float *p = net->tws;
-    w.H = p;
-    p += K * BW;
-    w.F1 = p;
-    p += K * BW;
-    w.A = p;
-    p += K * BW;
-    w.O = p;
-    p += K * BW;
-    w.HA = p;
-    p += Hh * BW;
-    w.HO = p;
-    p += Hh * BW;
-    w.dcur = p;
-    p += BW;
-    w.dnext = p;
-    p += BW;
-    w.dh = p;
-    p += BW;
-    w.dpre = p;
-    p += B;
-    w.sq = p;
-    p += B;
-    w.split = p;
-    w.split_floats = split;
+    auto take = [&](size_t n) {
+        float *q = p;
+        p += n;
+        return q;
+    };
+    a.F1 = take(K * BW);
+    a.O = take(K * BW);
+    a.DH = take(K * BW);
+    a.DA = take(K * BW);
+    a.HO = take(Hd * BW);
+    a.DY = take(Hd * BW);
+    a.dpre = take(B);
+    a.sq = take(B);
     return DS_OK;
 }
 
@@ -543,11 +418,12 @@ static ds_status mlp_loss_grad(ds_net *net, const float *z, const float *target,
     return DS_OK;
 }
 
-// Loss and gradient of a minibatch: forward keeping pre-activations, then
-// backpropagation layer by layer; every parameter gradient is written exactly once.
-// FP32 arithmetic, or (train_prec BF16) every GEMM on the BF16 matrix cores with FP32
-// accumulation (operands rounded once, or as hi + lo pairs for the forward W x W products);
-// epilogues, reductions and the loss stay FP32.
+// Loss and gradient of a minibatch: the forward chain keeping every layer's outputs, the
+// backward chain of pre-activation gradients, then all weight gradients at once.  FP32
+// arithmetic, or (train_prec BF16) every product on the BF16 matrix cores with FP32
+// accumulation (operands rounded once, or as hi + lo pairs for the forward W x W products:
+// a single BF16 rounding of these, carried through the residual stream of all blocks, moves
+// the loss and thus every gradient); biases, reductions and the loss stay FP32.
 ds_status loss_grad(ds_net *net, const float *z, const float *target, int B, float *loss,
                     float *grad)
 {
@@ -555,164 +431,25 @@ ds_status loss_grad(ds_net *net, const float *z, const float *target, int B, flo
         return mlp_loss_grad(net, z, target, B, loss, grad);
     hipStream_t s = net->ctx->stream;
     const bool bf = net->train_prec == DS_PREC_BF16;
-    const int K = net->K, W = net->W, Hn = net->H, D = kStencil * K + 1;
-    const float *th = net->theta;
-    ParamOffsets po = param_offsets(K, W, Hn);
-    TrainWs w;
-    DS_TRY(train_ws(net, B, w));
-    auto mm = [&](const StridedGemm &g) {
-        return bf ? gemm_bf16(s, g, w.split, w.split_floats)
-                  : gemm_strided(s, g, w.split, w.split_floats);
-    };
-    // forward products of the W x W layers (W1, W2, trailing): in BF16 their operands as
-    // hi + lo pairs.  A single BF16 rounding of these operands, carried through the residual
-    // stream of all blocks, moves the loss and thus every gradient; the descriptor layers
-    // and the backward products keep one BF16 term
-    auto mmw = [&](const StridedGemm &g) {
-        return bf ? gemm_bf16(s, g, w.split, w.split_floats, true)
-                  : gemm_strided(s, g, w.split, w.split_floats);
-    };
-    const size_t BW = (size_t)B * W;
-    auto H = [&](int k) { return w.H + k * BW; };
-    auto F1 = [&](int k) { return w.F1 + k * BW; };
-    auto A = [&](int k) { return w.A + k * BW; };
-    auto O = [&](int k) { return w.O + k * BW; };  // output of block k
-    auto HA = [&](int m) { return w.HA + m * BW; };
-    auto HO = [&](int m) { return w.HO + m * BW; };
-    // ---- forward
-    for (int k = 0; k < K; ++k) {
-        GemmArgs g1 = {};
-        g1.M = B;
-        g1.N = W;
-        g1.A1 = z + (int64_t)k * kStencil;
-        g1.lda1 = D;
-        g1.K1 = kStencil;
-        g1.B1 = th + po.V[k];
-        g1.ldb1 = 226;
-        if (k > 0) {
-            g1.A2 = O(k - 1);
-            g1.lda2 = W;
-            g1.K2 = W;
-            g1.B2 = th + po.W1[k];
-            g1.ldb2 = W;
-        }
-        g1.g = z + (int64_t)kStencil * K;
-        g1.ldg = D;
-        g1.gw = th + po.V[k] + 225;
-        g1.ldgw = 226;
-        g1.bias = th + po.b1[k];
-        g1.C = F1(k);
-        g1.ldc = W;
-        g1.pre = H(k);
-        g1.ldpre = W;
-        g1.relu = 1;
-        if (bf) {
-            DS_TRY(mm({B, W, kStencil, z + (int64_t)k * kStencil, D, 1, th + po.V[k], 1, 226, H(k), W,
-                       0}));
-            if (k > 0)
-                DS_TRY(mmw({B, W, W, O(k - 1), W, 1, th + po.W1[k], 1, W, H(k), W, 1}));
-            DS_TRY(layer_epilogue(s, B, W, H(k), W, z + (int64_t)kStencil * K, D,
-                                  th + po.V[k] + 225, 226, th + po.b1[k], nullptr, 0, F1(k), W));
-        } else {
-            DS_TRY(gemm_f32(s, g1));
-        }
-        GemmArgs g2 = {};
-        g2.M = B;
-        g2.N = W;
-        g2.A1 = F1(k);
-        g2.lda1 = W;
-        g2.K1 = W;
-        g2.B1 = th + po.W2[k];
-        g2.ldb1 = W;
-        g2.bias = th + po.b2[k];
-        if (k > 0) {
-            g2.R = O(k - 1);
-            g2.ldr = W;
-        }
-        g2.C = O(k);
-        g2.ldc = W;
-        g2.pre = A(k);
-        g2.ldpre = W;
-        g2.relu = 1;
-        if (bf) {
-            DS_TRY(mmw({B, W, W, F1(k), W, 1, th + po.W2[k], 1, W, A(k), W, 0}));
-            DS_TRY(layer_epilogue(s, B, W, A(k), W, nullptr, 0, nullptr, 0, th + po.b2[k],
-                                  k > 0 ? O(k - 1) : nullptr, W, O(k), W));
-        } else {
-            DS_TRY(gemm_f32(s, g2));
-        }
-    }
-    for (int m = 0; m < Hn; ++m) {
-        const bool last = m == Hn - 1;
-        GemmArgs g = {};
-        g.M = B;
-        g.N = last ? 1 : W;
-        g.A1 = m == 0 ? O(K - 1) : HO(m - 1);
-        g.lda1 = W;
-        g.K1 = W;
-        g.B1 = th + po.hw[m];
-        g.ldb1 = W;
-        g.bias = th + po.hb[m];
-        g.C = HO(m);
-        g.ldc = last ? 1 : W;
-        g.pre = HA(m);
-        g.ldpre = last ? 1 : W;
-        g.relu = 1;
-        if (bf) {
-            const int N = last ? 1 : W;
-            DS_TRY(mmw({B, N, W, g.A1, W, 1, th + po.hw[m], 1, W, HA(m), N, 0}));
-            DS_TRY(layer_epilogue(s, B, N, HA(m), N, nullptr, 0, nullptr, 0, th + po.hb[m], nullptr,
-                                  0, HO(m), N));
-        } else {
-            DS_TRY(gemm_f32(s, g));
-        }
-    }
-    // ---- loss and d loss / d (final pre-activation)
-    DS_TRY(loss_head(s, HA(Hn - 1), target, B, w.dpre, w.sq, loss));
+    ChainArgs a = {};
+    a.z = z;
+    a.theta = net->theta;
+    a.pack = bf ? net->chain16 : net->chain;
+    a.M = B;
+    a.K = net->K;
+    a.W = net->W;
+    a.H = net->H;
+    a.target = target;
+    DS_TRY(train_ws(net, B, a));
+    if (!grad)  // the loss alone keeps no activations
+        a.F1 = a.O = a.HO = nullptr;
+    DS_TRY(chain_forward(s, a, bf));
+    if (loss)
+        DS_TRY(loss_mean(s, a.sq, B, loss));
     if (!grad)
         return DS_OK;
-    // ---- trailing layers, last first; dcur = d loss / d (layer pre-activation)
-    const float *dY = w.dpre;
-    int ldy = 1;
-    for (int m = Hn - 1; m >= 0; --m) {
-        const int rows = m == Hn - 1 ? 1 : W;
-        const float *in = m == 0 ? O(K - 1) : HO(m - 1);
-        if (m < Hn - 1) {
-            DS_TRY(relu_mask(s, w.dcur, W, HA(m), W, B, W));
-            dY = w.dcur;
-            ldy = W;
-        }
-        // dW = dY^T in, db = column sums of dY
-        DS_TRY(mm({rows, W, B, dY, 1, ldy, in, W, 1, grad + po.hw[m], W, 0}));
-        DS_TRY(colsum(s, dY, ldy, B, rows, grad + po.hb[m], w.split));
-        // d in = dY W
-        DS_TRY(mm({B, W, rows, dY, ldy, 1, th + po.hw[m], W, 1, w.dnext, W, 0}));
-        std::swap(w.dcur, w.dnext);
-    }
-    // ---- blocks, last first; dcur = d loss / d o^k
-    for (int k = K - 1; k >= 0; --k) {
-        float *da = w.dcur;
-        DS_TRY(relu_mask(s, da, W, A(k), W, B, W));
-        DS_TRY(mm({W, W, B, da, 1, W, F1(k), W, 1, grad + po.W2[k], W, 0}));
-        DS_TRY(colsum(s, da, W, B, W, grad + po.b2[k], w.split));
-        // dh = (da W2) masked by h > 0
-        DS_TRY(mm({B, W, W, da, W, 1, th + po.W2[k], W, 1, w.dh, W, 0}));
-        DS_TRY(relu_mask(s, w.dh, W, H(k), W, B, W));
-        // dV over the 225 stencil columns and the gamma column
-        DS_TRY(mm({W, kStencil, B, w.dh, 1, W, z + (int64_t)k * kStencil, D, 1,
-                                grad + po.V[k], 226, 0}));
-        DS_TRY(mm({W, 1, B, w.dh, 1, W, z + (int64_t)kStencil * K, D, 1,
-                                grad + po.V[k] + 225, 226, 0}));
-        DS_TRY(colsum(s, w.dh, W, B, W, grad + po.b1[k], w.split));
-        if (k > 0) {
-            DS_TRY(mm({W, W, B, w.dh, 1, W, O(k - 1), W, 1, grad + po.W1[k], W, 0}));
-            // d o^{k-1} = da + dh W1
-            DS_TRY(copy_f32(s, w.dnext, da, (int64_t)BW));
-            DS_TRY(mm({B, W, W, w.dh, W, 1, th + po.W1[k], W, 1, w.dnext, W, 1}));
-            std::swap(w.dcur, w.dnext);
-        }
-    }
-    return DS_OK;
+    DS_TRY(chain_backward(s, a, bf));
+    return weight_grads(s, a, grad, bf);
 }
 
 }  // namespace
@@ -1177,15 +914,21 @@ ds_status ds_net_create(ds_ctx *ctx, const ds_net_desc *desc, ds_net **out)
     n->W = desc->W;
     n->H = desc->H;
     n->n_params = ds_net_param_count(desc);
-    if (hipMalloc(&n->theta, sizeof(float) * n->n_params) != hipSuccess) {
-        delete n;
+    const size_t cb = chain_pack_bytes(n->K, n->W, n->H, false);
+    const size_t cb16 = chain_pack_bytes(n->K, n->W, n->H, true);
+    if (hipMalloc(&n->theta, sizeof(float) * n->n_params) != hipSuccess ||
+        hipMalloc(&n->chain, cb) != hipSuccess || hipMalloc(&n->chain16, cb16) != hipSuccess) {
+        ds_net_destroy(n);
         set_error("ds_net_create: out of device memory");
         return DS_ERR_OOM;
     }
     hipError_t e = hipMemsetAsync(n->theta, 0, sizeof(float) * n->n_params, ctx->stream);
+    if (e == hipSuccess)
+        e = hipMemsetAsync(n->chain, 0, cb, ctx->stream);
+    if (e == hipSuccess)
+        e = hipMemsetAsync(n->chain16, 0, cb16, ctx->stream);
     if (e != hipSuccess) {
-        (void)hipFree(n->theta);
-        delete n;
+        ds_net_destroy(n);
         return hip_fail(e, "ds_net_create");
     }
     *out = n;
@@ -1241,6 +984,14 @@ ds_status ds_net_create_mlp(ds_ctx *ctx, int32_t K, int32_t n_layers, const int3
     return DS_OK;
 }
 
+// The packed copies of the progressive network's parameters follow theta.
+static ds_status refresh_packed(ds_net *net)
+{
+    hipStream_t s = net->ctx->stream;
+    ds_status st = chain_pack(s, net);
+    return st || fused_tiles(net->W) <= 0 ? st : fused_pack_bf16(s, net);
+}
+
 ds_status ds_net_set_params(ds_net *net, const float *theta_host, int64_t n)
 {
     DS_CHECK(net && theta_host, DS_ERR_INVALID_ARG, "ds_net_set_params: NULL argument");
@@ -1253,8 +1004,8 @@ ds_status ds_net_set_params(ds_net *net, const float *theta_host, int64_t n)
     DS_HIP(hipStreamSynchronize(net->ctx->stream));
     DS_HIP(hipMemcpy(net->theta, theta_host, sizeof(float) * n, hipMemcpyHostToDevice));
     net->fp8_ready = false;
-    if (net->kind == 0 && fused_tiles(net->W) > 0) {
-        ds_status st = fused_pack_bf16(net->ctx->stream, net);
+    if (net->kind == 0) {
+        ds_status st = refresh_packed(net);
         if (st)
             return st;
         DS_HIP(hipStreamSynchronize(net->ctx->stream));
@@ -1283,6 +1034,8 @@ ds_status ds_net_destroy(ds_net *net)
     (void)hipFree(net->vec);
     (void)hipFree(net->fmap);
     (void)hipFree(net->vmap);
+    (void)hipFree(net->chain);
+    (void)hipFree(net->chain16);
     (void)hipFree(net->frag_fp8);
     (void)hipFree(net->vec8);
     (void)hipFree(net->tws);
@@ -1986,9 +1739,7 @@ static ds_status train_step_body(ds_net *net, ds_adam *opt, const float *z,
     if (st)
         return st;
     net->fp8_ready = false;
-    if (net->kind == 0 && fused_tiles(net->W) > 0)
-        return fused_pack_bf16(net->ctx->stream, net);
-    return DS_OK;
+    return net->kind == 0 ? refresh_packed(net) : DS_OK;
 }
 
 ds_status ds_train_step(ds_net *net, ds_adam *opt, const float *z, const float *target_log1p,

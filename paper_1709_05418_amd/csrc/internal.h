@@ -124,6 +124,9 @@ struct ds_net {
     float *vec8 = nullptr;        // biases and final layer, scaled to the FP8 form's units
     std::vector<int32_t> fp8_exps;  // log2 units of the activations, then matrix exponents
     bool fp8_ready = false;       // FP8 form matches the current parameters
+    // the matrices in the layer chains' fragment order, FP32 and BF16 (chain.hip); like the
+    // fragments above they follow every change of theta
+    void *chain = nullptr, *chain16 = nullptr;
     // training workspace (activations and gradients of one minibatch)
     float *tws = nullptr;
     size_t tws_floats = 0;
@@ -213,21 +216,27 @@ ds_status gather_plain(hipStream_t s, const GatherArgs &a, int64_t p0, int64_t n
                        void *z, int64_t ldz, uint8_t *flags);
 ds_status mask_invalid(hipStream_t s, const uint8_t *flags, int64_t n, float *out, float *pre);
 
-// mlp.hip: C = act(A1 B1^T + A2 B2^T + g (x) gw + bias + R), row-major, B rows = outputs
-struct GemmArgs {
-    int M, N;
-    const float *A1; int lda1; int K1; const float *B1; int ldb1;
-    const float *A2; int lda2; int K2; const float *B2; int ldb2;
-    const float *g; int ldg; const float *gw; int ldgw;  // rank-1 term (may be null)
-    const float *bias;
-    const float *R; int ldr;                           // residual (may be null)
-    float *C; int ldc;
-    float *pre; int ldpre;                             // pre-activation copy (may be null)
-    int relu;
+// chain.hip: all layers of the progressive network on M rows.  Forward reads z ([M][225K+1])
+// and theta; every output may be NULL: activations after ReLU F1, O ([K][M][W]) and HO
+// ([H-1][M][W]), out, pre ([M]), the running maxima amax (K + 1 + H-1 float bits), and with
+// target the per-row squared loss sq and d loss / d pre dpre.  Backward reads dpre and the
+// activations and writes the pre-activations' gradients DA, DH ([K][M][W]; second and first
+// layer of each block) and DY ([H-1][M][W]).
+struct ChainArgs {
+    const float *z, *theta;
+    const void *pack;  // the network's matrices in the form's fragment order (chain_pack)
+    int64_t M;
+    int K, W, H;
+    float *F1, *O, *HO, *out, *pre, *sq, *dpre;
+    const float *target;
+    float *DA, *DH, *DY;
+    unsigned *amax;
+    int split_v, split_w, split_l;  // set by chain_forward: sums formed in two parts
 };
-ds_status gemm_f32(hipStream_t s, const GemmArgs &a);
-// out = max(out, max |x|) over n floats, as the bit pattern of a non-negative float
-ds_status amax_into(hipStream_t s, const float *x, int64_t n, unsigned *out);
+size_t chain_pack_bytes(int K, int W, int H, bool bf16);
+ds_status chain_pack(hipStream_t s, const ds_net *net);  // both forms, from net->theta
+ds_status chain_forward(hipStream_t s, const ChainArgs &a, bool bf16);
+ds_status chain_backward(hipStream_t s, const ChainArgs &a, bool bf16);
 
 // train.hip: C (+)= A B with A(m, k) = A[m sam + k sak], B(k, n) = B[k sbk + n sbn]
 struct StridedGemm {
@@ -255,14 +264,16 @@ ds_status relu_mask(hipStream_t s, float *x, int ldx, const float *pre, int ldp,
 // column sums in a fixed order; scratch holds colsum_scratch(C) floats
 ds_status colsum(hipStream_t s, const float *d, int ldd, int R, int C, float *db, float *scratch);
 int colsum_scratch(int C);
+// every weight and bias gradient of the progressive network, canonical order, from the
+// activations and gradients of a forward and backward chain
+ds_status weight_grads(hipStream_t s, const ChainArgs &a, float *grad, bool bf16);
+ds_status loss_mean(hipStream_t s, const float *sq, int B, float *loss);
 ds_status loss_head(hipStream_t s, const float *pre, const float *t, int B, float *dpre, float *sq,
                     float *loss);
 // one Adam step: the step count and bias corrections advance on the device (state:
 // {lr, 1 - b1^t, 1 - b2^t}), then every parameter is updated
 ds_status adam_update(hipStream_t s, float *theta, float *m, float *v, const float *grad,
                       int64_t n, float b1, float b2, float eps, int64_t *steps, float *state);
-// dst = src (n floats), as a kernel
-ds_status copy_f32(hipStream_t s, float *dst, const float *src, int64_t n);
 
 // fused.hip
 int fused_tiles(int W);

@@ -446,6 +446,262 @@ __global__ void __launch_bounds__(256) k_gemm_bf16(StridedGemm g, int kc, float 
             }
 }
 
+// ---------------------------------------------------------------- weight gradients
+// All weight and bias gradients of the progressive network in one launch: every matrix's
+// gradient is dY^T X over the minibatch's rows (dY the layer's pre-activation gradients, X
+// its inputs), a workgroup per 64 x 64 tile, some 500 of them for the paper's network, so no
+// product needs splitting; the blocks of a matrix's first tile column also add up dY's
+// columns, in FP32, for the bias.  (29 products of 4 to 16 tiles each, launched one by one
+// with their split sums and column sums, took 0.9 ms of a 1024-row step.)  Sums over more
+// than kFlush rows are added in parts of kFlush, in order.
+constexpr int kFlush = 1024;
+
+struct GradTile {
+    StridedGemm g;
+    float *db;       // bias gradient of the tile's rows, or NULL
+    int m0, n0;
+    int64_t last;    // what column N - 1 of the operand lies further on (the gamma input)
+};
+
+__device__ __forceinline__ GradTile grad_tile(const ChainArgs &a, float *grad, int b)
+{
+    const int W = a.W, K = a.K, H = a.H, tm = (W + 63) / 64, tv = (kStencil + 1 + 63) / 64;
+    const int64_t w2 = (int64_t)W * W, MW = a.M * W;
+    const int D = kStencil * K + 1;
+    // canonical parameter vector: per block V, W1 (from the second on), b1, W2, b2
+    auto block = [&](int k) { return k * (226 * (int64_t)W + w2 + 2 * W) + (k > 1 ? k - 1 : 0) * w2; };
+    auto b1 = [&](int k) { return block(k) + 226 * (int64_t)W + (k > 0 ? w2 : 0); };
+    auto head = [&](int m) { return block(K) + m * (w2 + W); };
+    GradTile t = {};
+    t.g.K = (int)a.M;
+    t.g.M = W;
+    t.g.sam = 1;
+    t.g.sak = W;
+    t.g.N = W;
+    t.g.sbk = W;
+    t.g.sbn = 1;
+    t.g.ldc = W;
+    int nt = tm;
+    if (b < K * tm * tv) {  // V and gamma of block k
+        const int k = b / (tm * tv);
+        b -= k * tm * tv;
+        nt = tv;
+        t.g.A = a.DH + k * MW;
+        t.g.B = a.z + k * kStencil;
+        t.g.sbk = D;
+        t.g.N = kStencil + 1;
+        t.g.C = grad + block(k);
+        t.g.ldc = kStencil + 1;
+        t.db = grad + b1(k);
+        t.last = (int64_t)(K - 1 - k) * kStencil;
+    } else if ((b -= K * tm * tv) < (K - 1) * tm * tm) {  // W1 of blocks 2..K
+        const int k = b / (tm * tm) + 1;
+        b -= (k - 1) * tm * tm;
+        t.g.A = a.DH + k * MW;
+        t.g.B = a.O + (k - 1) * MW;
+        t.g.C = grad + block(k) + 226 * (int64_t)W;
+    } else if ((b -= (K - 1) * tm * tm) < K * tm * tm) {  // W2
+        const int k = b / (tm * tm);
+        b -= k * tm * tm;
+        t.g.A = a.DA + k * MW;
+        t.g.B = a.F1 + k * MW;
+        t.g.C = grad + b1(k) + W;
+        t.db = grad + b1(k) + W + w2;
+    } else {  // trailing layers, the scalar one last
+        b -= K * tm * tm;
+        const int m = min(b / (tm * tm), H - 1);
+        b -= m * tm * tm;
+        t.g.B = m == 0 ? a.O + (K - 1) * MW : a.HO + (m - 1) * MW;
+        t.g.C = grad + head(m);
+        t.g.A = a.DY + m * MW;
+        t.db = grad + head(m) + w2;
+        if (m == H - 1) {
+            t.g.A = a.dpre;
+            t.g.M = 1;
+            t.g.sak = 1;
+            t.db = grad + head(m) + W;
+        }
+    }
+    t.m0 = b / nt * 64;
+    t.n0 = b % nt * 64;
+    if (t.n0 > 0)
+        t.db = nullptr;
+    return t;
+}
+
+int grad_tiles(int K, int W, int H)
+{
+    const int tm = (W + 63) / 64, tv = (kStencil + 1 + 63) / 64;
+    return K * tm * tv + (2 * K - 1 + H - 1) * tm * tm + tm;
+}
+
+// The bias gradient of the tile's rows: part q of row r in red[r][q], added in order.
+__device__ __forceinline__ void bias_sum(float (*red)[4], int r, int q, float s, const GradTile &t)
+{
+    __syncthreads();
+    red[r][q] = s;
+    __syncthreads();
+    const int m = threadIdx.x;
+    if (m < 64 && t.m0 + m < t.g.M)
+        t.db[t.m0 + m] = ((red[m][0] + red[m][1]) + red[m][2]) + red[m][3];
+}
+
+__global__ void __launch_bounds__(256) k_grad_bf16(ChainArgs a, float *grad)
+{
+    __shared__ __attribute__((aligned(16))) __bf16 As[TM][TKP];  // [row][k]
+    __shared__ __attribute__((aligned(16))) __bf16 Bt[TN][TKP];  // [col][k]
+    __shared__ float red[64][4];
+    const GradTile t = grad_tile(a, grad, blockIdx.x);
+    const StridedGemm &g = t.g;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int g4 = lane >> 4, n16 = lane & 15;
+    const int wr = (w >> 1) * 32, wc = (w & 1) * 32;
+    const Stage sa = stage_of(g.A, g.sam, g.sak, t.m0, g.M, 0, tid);
+    Stage sb = stage_of(g.B, g.sbn, g.sbk, t.n0, g.N, 0, tid);
+    if (t.n0 + (tid & 63) == g.N - 1)  // the operand's columns are never read along k
+        sb.p += t.last;
+    f4 acc[2][2], sum[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+            acc[i][j] = sum[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+    float va[NE], vb[NE], bias = 0.f;
+    sa.load(0, g.K, va);
+    sb.load(0, g.K, vb);
+    for (int k0 = 0; k0 < g.K; k0 += TK) {
+        stage_store<false>(As, nullptr, sa, tid, va);
+        stage_store<false>(Bt, nullptr, sb, tid, vb);
+        if (t.db) {
+            float s = 0.f;
+#pragma unroll
+            for (int j = 0; j < NE; ++j)
+                s += va[j];
+            bias += s;
+        }
+        __syncthreads();
+        if (k0 + TK < g.K) {
+            sa.load(k0 + TK, g.K, va);
+            sb.load(k0 + TK, g.K, vb);
+        }
+#pragma unroll
+        for (int ks = 0; ks < TK; ks += 32) {
+            bf16x8 x[2], y[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                x[i] = *reinterpret_cast<const bf16x8 *>(&As[wr + 16 * i + n16][ks + 8 * g4]);
+                y[i] = *reinterpret_cast<const bf16x8 *>(&Bt[wc + 16 * i + n16][ks + 8 * g4]);
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[i], y[j], acc[i][j], 0, 0, 0);
+        }
+        if ((k0 + TK) % kFlush == 0) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    sum[i][j] += acc[i][j];
+                    acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+                }
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int row = t.m0 + wr + 16 * i + 4 * g4 + q, col = t.n0 + wc + 16 * j + n16;
+                if (row < g.M && col < g.N)
+                    g.C[(int64_t)row * g.ldc + col] = sum[i][j][q] + acc[i][j][q];
+            }
+    if (t.db)
+        bias_sum(red, sa.kc ? tid >> 2 : tid & 63, sa.kc ? tid & 3 : tid >> 6, bias, t);
+}
+
+__global__ void __launch_bounds__(256) k_grad_f32(ChainArgs a, float *grad)
+{
+    __shared__ float As[BK][BM + 4];
+    __shared__ float Bs[BK][BN + 4];
+    __shared__ float red[64][4];
+    const GradTile t = grad_tile(a, grad, blockIdx.x);
+    const StridedGemm &g = t.g;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int wm = (w & 1) * 32, wn = (w >> 1) * 32;
+    const int li = lane & 15, lk = lane >> 4;
+    const StageF sa = stage_f(g.A, g.sam, g.sak, t.m0, g.M, 0, tid);
+    StageF sb = stage_f(g.B, g.sbn, g.sbk, t.n0, g.N, 0, tid);
+    if (t.n0 + (tid & 63) == g.N - 1)
+        sb.p += t.last;
+    f4v acc[2][2], sum[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+            acc[i][j] = sum[i][j] = f4v{0.f, 0.f, 0.f, 0.f};
+    float va[NF], vb[NF], bias = 0.f, part = 0.f;
+    sa.load(0, g.K, va);
+    sb.load(0, g.K, vb);
+    for (int k0 = 0; k0 < g.K; k0 += BK) {
+        sa.store(As, va);
+        sb.store(Bs, vb);
+        if (t.db) {
+#pragma unroll
+            for (int j = 0; j < NF; ++j)
+                part += va[j];
+        }
+        __syncthreads();
+        if (k0 + BK < g.K) {
+            sa.load(k0 + BK, g.K, va);
+            sb.load(k0 + BK, g.K, vb);
+        }
+#pragma unroll
+        for (int ks = 0; ks < BK; ks += 4) {
+            float x[2], y[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                x[i] = As[ks + lk][wm + 16 * i + li];
+                y[i] = Bs[ks + lk][wn + 16 * i + li];
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[i], y[j], acc[i][j], 0, 0, 0);
+        }
+        // parts of 64 rows: running sums at least as short as split products had
+        if ((k0 + BK) % 64 == 0) {
+            bias += part;
+            part = 0.f;
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    sum[i][j] += acc[i][j];
+                    acc[i][j] = f4v{0.f, 0.f, 0.f, 0.f};
+                }
+        }
+        __syncthreads();
+    }
+    bias += part;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int m = t.m0 + wm + 16 * i + 4 * lk + v, n = t.n0 + wn + 16 * j + li;
+                if (m < g.M && n < g.N)
+                    g.C[(int64_t)m * g.ldc + n] = sum[i][j][v] + acc[i][j][v];
+            }
+    if (t.db)
+        bias_sum(red, sa.row, sa.kc ? tid & 3 : tid >> 6, bias, t);
+}
+
 __global__ void __launch_bounds__(256) k_splitk_sum(const float *P, int S, StridedGemm g)
 {
     const int64_t n = (int64_t)g.M * g.N;
@@ -578,6 +834,24 @@ ds_status colsum(hipStream_t s, const float *d, int ldd, int R, int C, float *db
     return DS_OK;
 }
 
+ds_status weight_grads(hipStream_t s, const ChainArgs &a, float *grad, bool bf16)
+{
+    const unsigned blocks = (unsigned)grad_tiles(a.K, a.W, a.H);
+    if (bf16)
+        k_grad_bf16<<<blocks, 256, 0, s>>>(a, grad);
+    else
+        k_grad_f32<<<blocks, 256, 0, s>>>(a, grad);
+    DS_HIP(hipGetLastError());
+    return DS_OK;
+}
+
+ds_status loss_mean(hipStream_t s, const float *sq, int B, float *loss)
+{
+    k_loss_mean<<<1, 256, 0, s>>>(sq, B, loss);
+    DS_HIP(hipGetLastError());
+    return DS_OK;
+}
+
 ds_status loss_head(hipStream_t s, const float *pre, const float *t, int B, float *dpre, float *sq,
                     float *loss)
 {
@@ -593,22 +867,6 @@ ds_status adam_update(hipStream_t s, float *theta, float *m, float *v, const flo
 {
     k_adam_prep<<<1, 64, 0, s>>>(steps, state, b1, b2);
     k_adam<<<grid1(n), 256, 0, s>>>(theta, m, v, grad, n, b1, b2, eps, state);
-    DS_HIP(hipGetLastError());
-    return DS_OK;
-}
-
-__global__ void __launch_bounds__(256) k_copy(float *dst, const float *src, int64_t n)
-{
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x)
-        dst[i] = src[i];
-}
-
-ds_status copy_f32(hipStream_t s, float *dst, const float *src, int64_t n)
-{
-    if (n <= 0)
-        return DS_OK;
-    k_copy<<<grid1(n), 256, 0, s>>>(dst, src, n);
     DS_HIP(hipGetLastError());
     return DS_OK;
 }
