@@ -1301,6 +1301,291 @@ __global__ void __launch_bounds__(64 * NW, 2) k_fused_reg(FusedArgs a,
     }
 }
 
+// Few points: one workgroup computes PW points (16, or 4 for a handful), wave w the output
+// tile w of every layer.  The waves first gather all K levels together into LDS, as the
+// operands of the stencil chunks (a wave takes one chunk of 16 / PW levels at a time); the
+// layers then pass their outputs, packed as the next layer's operands, through LDS, and each
+// wave streams its own tile's weight fragments from L2 into registers one layer ahead.  Every
+// tile's products keep the register kernel's order, so the results are the same bit by bit;
+// the samples are clamped, so one launch does both passes' work.
+//
+// What bounds it: a compute unit takes all weights once through its vector memory path
+// (2.8 MB at K = 10, W = 200: 18 us at 64 B per clock) and PW points' cells (16 points:
+// 36000 cell reads, each of scattered points a cache line of its own).  37 scattered points
+// of the 10 x 200 network: 122 us in the register kernel's two passes, 49 us here; 4096
+// points of a 6 x 64 network: 43 and 19 us.  (The next layer's loads held before this
+// layer's products: 42.2 us instead of 41.2 us on device.)
+constexpr int few_waves(int MT) { return MT < 8 ? 8 : MT; }
+constexpr int few_entries(int MT, bool f8) { return f8 ? 2 * ((MT + 7) / 8) : (MT + 1) / 2; }
+
+// LDS: the levels' stencil chunks (later the last activations), two layers' operands
+constexpr size_t few_lds(int MT, bool f8, int K)
+{
+    const size_t z = std::max((size_t)K * 8 * 64, (size_t)MT * 64);
+    return (z + 2 * (size_t)few_entries(MT, f8) * 64) * sizeof(uint4);
+}
+
+template <int MT, bool F8, int PW>
+__global__ void __launch_bounds__(64 * few_waves(MT)) k_fused_few(FusedArgs a,
+                                                                  const uint4 *__restrict__ frags,
+                                                                  const float *__restrict__ vec)
+{
+    constexpr int NWV = few_waves(MT), C2 = (MT + 1) / 2, WP = 16 * MT;
+    constexpr int LV = 16 / PW;  // levels gathered together
+    constexpr bool FOLD = F8 ? MT % 8 != 0 : (MT & 1) != 0;  // see predict_points
+    constexpr int NE = few_entries(MT, F8);                 // operand entries of a layer
+    constexpr int N1 = F8 ? NE : MT / 2;                    // of those, W1's chunks
+    extern __shared__ __attribute__((aligned(16))) unsigned char few_smem[];
+    __shared__ float4 plane[32];
+    __shared__ float2 cols[24];
+    __shared__ PtGeom geom[PW];
+    __shared__ float gam[PW];
+    __shared__ FusedLevel lv[kMaxK];
+    uint4 *const zb = reinterpret_cast<uint4 *>(few_smem);  // [level][chunk][lane]
+    uint4 *const fb = zb + (a.K * 8 > MT ? a.K * 8 : MT) * 64, *const ob = fb + NE * 64;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t t = xcd_tile(blockIdx.x, a.n_tiles);
+    const FusedCloud &cl = a.cl[tile_cloud(a, t)];
+    const int64_t pl0 = (t - cl.tile_begin) * PW;
+
+    init_tables(tid, plane, cols);
+    if (tid >= 64 && tid < 64 + a.K)
+        lv[tid - 64] = cl.lvt[tid - 64];
+    if (tid < PW) {
+        const bool in = pl0 + tid < cl.P;
+        float x[3];
+        Frame fr;
+        const bool valid = point_frame(a, point_row(a, cl.p_begin + pl0 + tid, in), in, x, fr);
+        geom[tid] = make_geom(x, fr, cl.amin, valid);
+        gam[tid] = valid ? fr.gamma : 0.f;
+    }
+    // operands past the last tile: zero, or the ones that take a folded bias
+    for (int e = tid; e < 2 * NE * 64; e += 64 * NWV) {
+        uint4 v = {0u, 0u, 0u, 0u};
+        if (FOLD && (e & 63) < 16 && e / 64 % NE == (F8 ? MT / 4 : C2 - 1)) {
+            const uint32_t one = F8 ? 0x00383838u : 0x3F803F80u;  // see pack_fp8, bias_ones
+            const int d = F8 ? MT & 3 : 2;
+            v = uint4{d == 0 ? one : 0u, d == 1 ? one : 0u, d == 2 ? one : 0u, d == 3 ? one : 0u};
+        }
+        fb[e] = v;
+    }
+    __syncthreads();
+    {
+        // lane n + PW (g + 4 s): point n, lane group g, level s of the task's
+        const int n = lane & (PW - 1), g = (lane / PW) & 3, sub = lane / (4 * PW);
+        const int KG = (a.K + LV - 1) / LV, tasks = 7 * KG;
+        auto level = [&](int kg) { return min(kg * LV + (LV > 1 ? sub : 0), a.K - 1); };
+        auto issue = [&](int task, Pending &pa, Pending &pb) {
+            const int c = task / KG;
+            const FusedLevel L = lv[level(task % KG)];
+            gcell_ptr cells = (gcell_ptr)L.cells;
+            PtLevel q;
+            level_from_geom(L, geom[n], q);
+            if (c < 6) {
+                issue_column<true>(cells, L, q, c, g, cols, pa, pb);
+            } else {
+                issue_table_half<true>(cells, L, q, 0, g, plane, pa);
+                issue_table_half<true>(cells, L, q, 1, g, plane, pb);
+            }
+        };
+        auto finish = [&](int task, const Pending &pa, const Pending &pb) {
+            f4 lo, hi;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                lo[j] = finish_one(pa.v[j], pa.fx[j], pa.t[j]);
+                hi[j] = finish_one(pb.v[j], pb.fx[j], pb.t[j]);
+            }
+            const int kg = task % KG;
+            if (LV == 1 || kg * LV + sub < a.K)
+                zb[(level(kg) * 8 + task / KG) * 64 + 16 * g + n] =
+                    __builtin_bit_cast(uint4, pack8(lo, hi));
+        };
+        Pending pa, pb, qa, qb;
+        int task = wave;
+        if (task < tasks)
+            issue(task, pa, pb);
+#pragma unroll 1
+        while (task < tasks) {
+            const int second = task + NWV, third = second + NWV;
+            if (second < tasks)
+                issue(second, qa, qb);
+            finish(task, pa, pb);
+            if (third < tasks)
+                issue(third, pa, pb);
+            if (second < tasks)
+                finish(second, qa, qb);
+            task = third;
+        }
+        // chunk 7: the last stencil sample, gamma, the inputs of b1's two parts
+#pragma unroll 1
+        for (int kg = NWV - 1 - wave; kg < KG; kg += NWV) {
+            const FusedLevel L = lv[level(kg)];
+            PtLevel q;
+            level_from_geom(L, geom[n], q);
+#pragma unroll
+            for (int i = 0; i < 3; ++i)  // the steps rounded before they are added, as there
+                asm volatile("" : "+v"(q.a[i]), "+v"(q.b[i]));
+            Pending p;
+            issue_one<true>((gcell_ptr)L.cells, L, q.u0[0] + 4.f * (q.a[0] + q.b[0]) + 8.f * q.c[0],
+                            q.u0[1] + 4.f * (q.a[1] + q.b[1]) + 8.f * q.c[1],
+                            q.u0[2] + 4.f * (q.a[2] + q.b[2]) + 8.f * q.c[2], p.v[0], p.fx[0],
+                            p.t[0]);
+            const float sv = finish_one(p.v[0], p.fx[0], p.t[0]), one = g == 1 ? 1.f : 0.f;
+            const f4 lo = f4{g == 0 ? sv : one, g == 0 ? gam[n] : one, 0.f, 0.f};
+            if (LV == 1 || kg * LV + sub < a.K)
+                zb[(level(kg) * 8 + 7) * 64 + 16 * g + n] =
+                    __builtin_bit_cast(uint4, pack8(lo, f4{0.f, 0.f, 0.f, 0.f}));
+        }
+    }
+
+    // the layers: this wave's tile (waves past the last tile only keep the barriers)
+    const bool mine = wave < MT;
+    const int n = lane & 15, g = lane >> 4;
+    const uint4 *next = frags + (mine ? wave : 0) * 64;  // this tile of the next chunk
+    const f4 z4 = f4{0.f, 0.f, 0.f, 0.f};
+    uint4 A1[8 + N1], A2[NE];
+    auto fetch = [&](uint4 *A, int count) {
+#pragma unroll
+        for (int c = 0; c < count; ++c)
+            A[c] = next[c * (MT * 64) + lane];
+        next += count * (MT * 64);
+    };
+    // acc += a W-wide layer's chunks times the operands x
+    auto layer = [&](const uint4 *A, int count, const uint4 *x, f4 acc) {
+        if constexpr (F8) {
+#pragma unroll
+            for (int c = 0; c < count; c += 2) {
+                const uint4 xl = x[c * 64 + lane], xh = x[(c + 1) * 64 + lane];
+                const fp8x32 A8 = {(int)A[c].x, (int)A[c].y, (int)A[c].z, (int)A[c].w,
+                                   (int)A[c + 1].x, (int)A[c + 1].y, (int)A[c + 1].z,
+                                   (int)A[c + 1].w};
+                const fp8x32 B8 = {(int)xl.x, (int)xl.y, (int)xl.z, (int)xl.w,
+                                   (int)xh.x, (int)xh.y, (int)xh.z, (int)xh.w};
+                acc = mfma_fp8(A8, B8, acc);
+            }
+        } else {
+#pragma unroll
+            for (int c = 0; c < count; ++c)
+                acc = mfma_bf16(A[c], __builtin_bit_cast(bf16x8, x[c * 64 + lane]), acc);
+        }
+        return acc;
+    };
+    // this tile's ReLU outputs (F8: at most 448) as the next layer's inputs
+    auto put = [&](uint4 *x, const f4 &v) {
+        if constexpr (F8) {
+            f4 c;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                c[i] = __builtin_amdgcn_fmed3f(v[i], 0.f, 448.f);
+            const int w = __builtin_amdgcn_cvt_pk_fp8_f32(c[0], c[1], 0, false);
+            reinterpret_cast<int *>(x)[(wave / 4 * 64 + lane) * 4 + (wave & 3)] =
+                __builtin_amdgcn_cvt_pk_fp8_f32(c[2], c[3], w, true);
+        } else {
+            const uint4 r = __builtin_bit_cast(uint4, pack8_relu(v, z4));
+            reinterpret_cast<uint2 *>(x)[(wave / 2 * 64 + lane) * 2 + (wave & 1)] =
+                uint2{r.x, r.y};
+        }
+    };
+    f4 O = z4;
+    if (mine)
+        fetch(A1, 8);
+    __syncthreads();
+#pragma unroll 1
+    for (int k = 0; k < a.K; ++k) {
+        if (mine) {
+            fetch(A2, NE);
+            f4 F = z4;
+#pragma unroll
+            for (int c = 0; c < 8; ++c)
+                F = mfma_bf16(A1[c], __builtin_bit_cast(bf16x8, zb[(k * 8 + c) * 64 + lane]), F);
+            if (k > 0) {
+                F = layer(A1 + 8, N1, ob, F);
+                // Where this path joins block 1's, the compiler counts the wait before F is
+                // read by the shorter BF16 product (8 states, the FP8 one takes 12: its
+                // first two results were read too early).
+                if constexpr (F8)
+                    asm volatile("s_nop 15" : "+v"(F));
+            }
+            put(fb, F);
+        }
+        __syncthreads();
+        if (mine) {
+            if (!FOLD)
+                O += *reinterpret_cast<const f4 *>(vec + (2 * k + 1) * WP + 16 * wave + 4 * g);
+            if (k + 1 < a.K)
+                fetch(A1, 8 + N1);
+            else if (a.H > 1)
+                fetch(A1, NE);
+            O = layer(A2, NE, fb, O);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                O[i] = fmaxf(O[i], 0.f);
+            put(ob, O);
+            if (!F8 && (MT & 1) && wave == MT - 1 && k + 1 < a.K) {  // its place in chunk 7
+                const uint4 r = __builtin_bit_cast(uint4, pack8(O, z4));
+                reinterpret_cast<uint2 *>(zb)[(((k + 1) * 8 + 7) * 64 + lane) * 2 + 1] =
+                    uint2{r.x, r.y};
+            }
+        }
+        __syncthreads();
+    }
+    const float *bh = vec + (size_t)a.K * 2 * WP;
+    uint4 *src = ob, *dst = fb;
+#pragma unroll 1
+    for (int h = 0; h < a.H - 1; ++h) {
+        if (mine) {
+            if (h + 1 < a.H - 1)
+                fetch(A2, NE);
+            const f4 b = FOLD ? z4 : *reinterpret_cast<const f4 *>(bh + h * WP + 16 * wave + 4 * g);
+            O = layer(A1, NE, src, b);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                O[i] = F8 ? __builtin_amdgcn_fmed3f(O[i], 0.f, 448.f) : fmaxf(O[i], 0.f);
+            put(dst, O);
+#pragma unroll
+            for (int c = 0; c < NE; ++c)
+                A1[c] = A2[c];
+        }
+        __syncthreads();
+        uint4 *const x = src;
+        src = dst;
+        dst = x;
+    }
+    // the scalar layer in the first wave
+    f4 *const last = reinterpret_cast<f4 *>(zb);
+    if (mine)
+        last[wave * 64 + lane] = O;
+    __syncthreads();
+    if (wave > 0)
+        return;
+    const float *wl = bh + (size_t)(a.H - 1) * WP;
+    const float bl = wl[WP];
+    float acc = 0.f;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+        const f4 w = *reinterpret_cast<const f4 *>(wl + 16 * mt + 4 * g), y = last[mt * 64 + lane];
+        acc += w[0] * y[0] + w[1] * y[1] + w[2] * y[2] + w[3] * y[3];
+    }
+    acc += __shfl_xor(acc, 16, 64);
+    acc += __shfl_xor(acc, 32, 64);
+    if (g == 0 && n < PW && pl0 + n < cl.P) {
+        const int64_t p = point_row(a, cl.p_begin + pl0 + n, true);
+        const float pre = acc + bl;
+        const bool valid = geom[n].d.w > 0.f;
+        a.out[p] = valid ? fmaxf(pre, 0.f) : 0.f;
+        if (a.pre)
+            a.pre[p] = valid ? pre : 0.f;
+        if (a.flags) {
+            float x[3];
+            Frame fr;
+            point_frame(a, p, true, x, fr);
+            a.flags[p] = valid ? point_flags(x, fr, cl.amin, cl.amax, cl.inv_mean)
+                               : (uint8_t)DS_FLAG_INVALID;
+        }
+    }
+}
+
 // Unclamped pass of the register kernel with two teams of four waves sharing one weight
 // ring (TeamRing): tiles of 128 points, team 0 taking points 0..63 and team 1 points
 // 64..127 of each, team 1 kTeamLag chunks behind.  Clouds that need the clamps and tiles
@@ -1709,6 +1994,26 @@ int64_t assign_tiles(FusedArgs &a, int64_t per)
     return t;
 }
 
+// The kernel for few points takes a launch up to kFewPoints: two workgroups of 16 points on
+// each of the 256 compute units.  Scattered points, register kernel and this one in us, at
+// 4096 / 8192 / 16384 points: 10 x 200 BF16 147, 72 / 142, 139 / 152, 275; 8 x 128 FP8 106,
+// 46 / 100, 78 / 109, 145; 6 x 64 BF16 84, 37 / 80, 61 / 87, 112; 4 x 16 BF16 65, 28 / 63,
+// 45 / 70, 83.  Up to kFewestPoints it takes four points per workgroup instead of 16, which
+// fills as many compute units as there are and shortens each one's gather: 16 and 4 points
+// in us, at 37 / 1000 / 2000 points: 10 x 200 BF16 73, 47 / 69, 52 / 68, 99; 6 x 64 21, 16 /
+// 33, 21 / 35, 28.
+constexpr int64_t kFewestPoints = 1024, kFewPoints = 8192;
+
+template <int MT, bool F8, int PW>
+ds_status launch_few(hipStream_t s, const ds_net *net, FusedArgs a)
+{
+    const int64_t tiles = assign_tiles(a, PW);
+    k_fused_few<MT, F8, PW><<<(unsigned)tiles, 64 * few_waves(MT), few_lds(MT, F8, a.K), s>>>(
+        a, F8 ? net->frag_fp8 : net->frag_bf16, F8 ? net->vec8 : net->vec);
+    DS_HIP(hipGetLastError());
+    return DS_OK;
+}
+
 template <int MT, int NW, int KIND, bool F8 = false>
 ds_status launch_kind(hipStream_t s, const ds_net *net, FusedArgs a, int grid)
 {
@@ -1771,6 +2076,15 @@ template <int MT>
 ds_status launch(hipStream_t s, const ds_net *net, const FusedArgs &a, const FusedVariant &v,
                  bool fp8)
 {
+    if (v.kind == DS_KERNEL_REGISTER && v.waves == 4 && v.grid == 0) {
+        int64_t P = 0;
+        for (int c = 0; c < a.n_clouds; ++c)
+            P += a.cl[c].P;
+        if (P > 0 && P <= kFewestPoints)
+            return fp8 ? launch_few<MT, true, 4>(s, net, a) : launch_few<MT, false, 4>(s, net, a);
+        if (P > 0 && P <= kFewPoints)
+            return fp8 ? launch_few<MT, true, 16>(s, net, a) : launch_few<MT, false, 16>(s, net, a);
+    }
     if (v.kind == DS_KERNEL_TEAMS) {
         if constexpr (MT < 16)
             return fp8 ? launch_teams<MT, true>(s, net, a, v.grid)
