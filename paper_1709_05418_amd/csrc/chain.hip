@@ -10,9 +10,9 @@
 // products per 16 rows, 67 us at 157 TFLOP/s over 256 compute units).  Per workgroup the
 // 1.3 M parameters of the paper's network pass through a compute unit's vector memory path
 // once (5.2 MB, 35 us at 64 B per clock).  K = 10, W = 200, H = 3: 500 rows forward FP32
-// 162 us, backward 101 us, 1024 rows BF16 109 and 41 us; loss and gradient of 500 rows
-// 1482 us as one GEMM (9 to 13 us) or two and an epilogue per layer, 302 us so; a training
-// step of 1024 rows 1364 and 276 us; 50000 rows' forward 2550 and 1899 us.
+// 160 us, backward 101 us, 1024 rows BF16 95 and 42 us; loss and gradient of 500 rows
+// 1482 us as one GEMM (9 to 13 us) or two and an epilogue per layer, 299 us so; a training
+// step of 1024 rows 1364 and 258 us; 50000 rows' forward 2550 and 1873 us.
 #include <algorithm>
 
 #include "internal.h"
@@ -30,7 +30,7 @@ struct __attribute__((packed, aligned(4))) f4u {  // 16 bytes at any float's add
 constexpr int kRows = 16;
 constexpr int kGroup = 4;  // k chunks loaded together
 // FP32 batches above this take 32 rows per workgroup, which halves the weights' traffic and
-// gives a wave two chains of products (50000 rows: 2080 us with 16, 1899 us with 32); up to
+// gives a wave two chains of products (50000 rows: 2080 us with 16, 1873 us with 32); up to
 // 16 rows on each of the 256 compute units, 32 would leave units idle.
 constexpr int64_t kFewRows = 4096;
 
@@ -261,16 +261,6 @@ __device__ __forceinline__ f4 load4(const float *p, uint32_t at, int f, int W)
     }
     return v;
 }
-// Four features' values from f on of a vector; past the last one its value, without a branch.
-__device__ __forceinline__ f4 bias4(const float *p, int f, int W)
-{
-    f4 v;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-        v[i] = p[(uint32_t)min(f + i, W - 1)];
-    return v;
-}
-
 __device__ __forceinline__ void amax_note(unsigned *out, const f4 &v)
 {
     float m = fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3])));
@@ -303,7 +293,7 @@ struct Params {
 // Packs every matrix (grid.y: K of V, then the W x W ones, then those transposed, then the
 // scalar layer), a thread per 16 bytes of a fragment.
 template <bool BF>
-__global__ void __launch_bounds__(256) k_chain_pack(const float *theta, int K, int W, int H, uint4 *out)
+__device__ __forceinline__ void pack(const float *theta, int K, int W, int H, uint4 *out)
 {
     constexpr int E = Form<BF>::E, CK = Form<BF>::CK;
     const Pack<BF> pk(out, K, W, H);
@@ -352,6 +342,17 @@ __global__ void __launch_bounds__(256) k_chain_pack(const float *theta, int K, i
     }
 }
 
+// Both packed copies in one launch (grid.z, 13.2 us): apart they took 8.2 and 6.2 us and a
+// launch more.
+__global__ void __launch_bounds__(256) k_chain_pack(const float *theta, int K, int W, int H, uint4 *f32,
+                                                    uint4 *bf16)
+{
+    if (blockIdx.z == 0)
+        pack<false>(theta, K, W, H, f32);
+    else
+        pack<true>(theta, K, W, H, bf16);
+}
+
 template <bool BF>
 __device__ __forceinline__ Weights<BF> &one_of(Weights<false> &a, Weights<BF> &b)
 {
@@ -379,6 +380,11 @@ __global__ void __launch_bounds__(1024, !BF && T == 1 ? 5 : 4) k_chain_forward(C
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 15, g = lane >> 4;
     const int64_t b0 = (int64_t)blockIdx.x * kR;
+    // per block gamma weights, b1, b2, then the trailing layers' biases, 16 to a tile: read
+    // where a layer ends, when every wave waits for them (from L2 there: 1024 rows BF16
+    // 109 us, from LDS 95 us)
+    float *const vl = reinterpret_cast<float *>(ob + (BF ? 2 : 0) * lo);
+    const int WP = nt / 4, nv = 3 * K + a.H - 1;
     bool in[T];  // this lane's rows n, n + 16, .. below M
 #pragma unroll
     for (int t = 0; t < T; ++t)
@@ -394,6 +400,14 @@ __global__ void __launch_bounds__(1024, !BF && T == 1 ? 5 : 4) k_chain_forward(C
 
     for (int e = tid; e < kR * ldz + (BF ? 4 : 1) * lo; e += nt)
         zb[e] = (X)0.f;
+    for (int e = tid; e < nv * WP; e += nt) {
+        const int v = e / WP, f = e - v * WP, k = v / 3;
+        float x = 0.f;
+        if (f < W)
+            x = v >= 3 * K ? P.hw(v - 3 * K)[(int64_t)W * W + f]
+                : v - 3 * k == 0 ? P.V(k)[226 * f + 225] : (v - 3 * k == 1 ? P.b1(k) : P.b2(k))[f];
+        vl[e] = x;
+    }
     __syncthreads();
     // A level's descriptors: unit u holds columns 64 (u & 3) + lane of row u >> 2; a wave takes
     // every waves-th unit, up to kZ of them in flight (fewer waves: one after another).
@@ -470,14 +484,13 @@ __global__ void __launch_bounds__(1024, !BF && T == 1 ? 5 : 4) k_chain_forward(C
             z_load(k + 1, zl_at);
         // first layer of the block: the gamma input, bias, ReLU
         {
-            const f4 bias = bias4(P.b1(k), f, W);
-            const float *gw = P.V(k) + 225;
+            const f4 gw = *reinterpret_cast<const f4 *>(vl + 3 * k * WP + f);
+            const f4 bias = *reinterpret_cast<const f4 *>(vl + (3 * k + 1) * WP + f);
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const float gv = gw[(uint32_t)min(f + i, W - 1) * 226u];
 #pragma unroll
                 for (int t = 0; t < T; ++t) {
-                    const float p = fmaf(gamma[t], gv, v.v[t][i]) + bias[i];
+                    const float p = fmaf(gamma[t], gw[i], v.v[t][i]) + bias[i];
                     v.v[t][i] = f + i < W ? fmaxf(p, 0.f) : 0.f;
                 }
             }
@@ -497,7 +510,7 @@ __global__ void __launch_bounds__(1024, !BF && T == 1 ? 5 : 4) k_chain_forward(C
             z_store(k + 1);
             load(wv, pk.V(k + 1) + tv, 0, ncz);
         }
-        const f4 bias = bias4(P.b2(k), f, W);
+        const f4 bias = *reinterpret_cast<const f4 *>(vl + (3 * k + 2) * WP + f);
 #pragma unroll
         for (int t = 0; t < T; ++t) {
             f4 &y = o.v[t];
@@ -555,7 +568,7 @@ __global__ void __launch_bounds__(1024, !BF && T == 1 ? 5 : 4) k_chain_forward(C
             }
             return;
         }
-        const f4 bias = bias4(hb, f, W);
+        const f4 bias = *reinterpret_cast<const f4 *>(vl + (3 * K + m) * WP + f);
 #pragma unroll
         for (int t = 0; t < T; ++t) {
             f4 &y = o.v[t];
@@ -648,18 +661,11 @@ __global__ void __launch_bounds__(1024) k_chain_backward(ChainArgs a)
     }
 }
 
-template <bool BF> size_t forward_lds(int W, int rows)
+template <bool BF> size_t forward_lds(int K, int W, int H, int rows)
 {
     return rows * (pitch<BF>(first_inputs<BF>(W)) + (BF ? 4 : 1) * pitch<BF>(W)) *
-           sizeof(Lds<BF>);
-}
-
-template <bool BF> void pack(hipStream_t s, const float *theta, int K, int W, int H, uint4 *out)
-{
-    const Pack<BF> pk(out, K, W, H);
-    const int nc = std::max(chunks<BF>(first_inputs<BF>(W)), chunks<BF>(W));
-    k_chain_pack<BF><<<dim3((unsigned)((pk.MT * nc * 64 + 255) / 256), (unsigned)(K + 2 * pk.nw() + 1)), 256,
-                       0, s>>>(theta, K, W, H, out);
+               sizeof(Lds<BF>) +
+           (size_t)(3 * K + H - 1) * ((W + 15) / 16 * 16) * sizeof(float);
 }
 
 }  // namespace
@@ -672,8 +678,11 @@ size_t chain_pack_bytes(int K, int W, int H, bool bf16)
 
 ds_status chain_pack(hipStream_t s, const ds_net *net)
 {
-    pack<false>(s, net->theta, net->K, net->W, net->H, static_cast<uint4 *>(net->chain));
-    pack<true>(s, net->theta, net->K, net->W, net->H, static_cast<uint4 *>(net->chain16));
+    const Pack<false> pk(net->chain, net->K, net->W, net->H);  // FP32: the most fragments
+    const int64_t n = (int64_t)pk.MT * chunks<false>(first_inputs<false>(net->W)) * 64;
+    k_chain_pack<<<dim3((unsigned)((n + 255) / 256), (unsigned)(net->K + 2 * pk.nw() + 1), 2), 256, 0, s>>>(
+        net->theta, net->K, net->W, net->H, static_cast<uint4 *>(net->chain),
+        static_cast<uint4 *>(net->chain16));
     DS_HIP(hipGetLastError());
     return DS_OK;
 }
@@ -692,12 +701,12 @@ ds_status chain_forward(hipStream_t s, const ChainArgs &args, bool bf16)
     a.split_l = rows < 64 && a.W > 128 && 2 * a.M <= (int64_t)16 * 226 * a.W;
     const unsigned blocks = (unsigned)((a.M + kRows - 1) / kRows), threads = 64 * ((a.W + 15) / 16);
     if (bf16)
-        k_chain_forward<true, 1><<<blocks, threads, forward_lds<true>(a.W, kRows), s>>>(a);
+        k_chain_forward<true, 1><<<blocks, threads, forward_lds<true>(a.K, a.W, a.H, kRows), s>>>(a);
     else if (a.M <= kFewRows)
-        k_chain_forward<false, 1><<<blocks, threads, forward_lds<false>(a.W, kRows), s>>>(a);
+        k_chain_forward<false, 1><<<blocks, threads, forward_lds<false>(a.K, a.W, a.H, kRows), s>>>(a);
     else
         k_chain_forward<false, 2>
-            <<<(blocks + 1) / 2, threads, forward_lds<false>(a.W, 2 * kRows), s>>>(a);
+            <<<(blocks + 1) / 2, threads, forward_lds<false>(a.K, a.W, a.H, 2 * kRows), s>>>(a);
     DS_HIP(hipGetLastError());
     return DS_OK;
 }

@@ -2281,12 +2281,21 @@ static void build_pack_maps(int K, int W, int H, std::vector<int32_t> &fmap,
 }
 
 namespace {
+// The fragments (n entries of map) and the vectors (nv of vmap) in one launch: apart they
+// took 6.0 and 5.0 us of a training step, so 6.3.
 __global__ void __launch_bounds__(256) k_pack_frags(const float *__restrict__ theta,
                                                     const int32_t *__restrict__ map, int64_t n,
-                                                    uint16_t *__restrict__ out)
+                                                    uint16_t *__restrict__ out,
+                                                    const int32_t *__restrict__ vmap, int64_t nv,
+                                                    float *__restrict__ vec)
 {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n + nv;
          i += (int64_t)gridDim.x * blockDim.x) {
+        if (i >= n) {
+            const int32_t at = vmap[i - n];
+            vec[i - n] = at >= 0 ? theta[at] : 0.f;
+            continue;
+        }
         const int32_t idx = map[i];
         float v = 0.f;
         if (idx >= 0) {
@@ -2300,16 +2309,6 @@ __global__ void __launch_bounds__(256) k_pack_frags(const float *__restrict__ th
         uint32_t u = __float_as_uint(v);
         u += 0x7FFFu + ((u >> 16) & 1u);  // round to nearest even
         out[i] = (uint16_t)(u >> 16);
-    }
-}
-__global__ void __launch_bounds__(256) k_pack_vec(const float *__restrict__ theta,
-                                                  const int32_t *__restrict__ map, int64_t n,
-                                                  float *__restrict__ out)
-{
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t idx = map[i];
-        out[i] = idx >= 0 ? theta[idx] : 0.f;
     }
 }
 }  // namespace
@@ -2352,9 +2351,10 @@ ds_status fused_pack_bf16(hipStream_t s, ds_net *net)
     if (st)
         return st;
     const int64_t nf = net->frag_count * 8, nv = net->vec_count;
-    k_pack_frags<<<(unsigned)((nf + 255) / 256 < 8192 ? (nf + 255) / 256 : 8192), 256, 0, s>>>(
-        net->theta, net->fmap, nf, reinterpret_cast<uint16_t *>(net->frag_bf16));
-    k_pack_vec<<<(unsigned)((nv + 255) / 256), 256, 0, s>>>(net->theta, net->vmap, nv, net->vec);
+    const int64_t blocks = (nf + nv + 255) / 256;
+    k_pack_frags<<<(unsigned)(blocks < 8192 ? blocks : 8192), 256, 0, s>>>(
+        net->theta, net->fmap, nf, reinterpret_cast<uint16_t *>(net->frag_bf16), net->vmap, nv,
+        net->vec);
     DS_HIP(hipGetLastError());
     return DS_OK;
 }
