@@ -417,12 +417,12 @@ constexpr int kOccWords = 2048;  // brick bits in LDS: at most 65536 bricks
 
 enum Phase { kNew, kStart, kBounce, kHit, kAimDelta, kAimRatio, kDelta, kRatio, kDone };
 
-// Blocks per compute unit: the walks without bounces are short of latency hiding rather than
-// registers.
-constexpr int walk_blocks(int kind) { return kind == kFirstHits || kind == kRecordDraws ? 5 : 4; }
+// Blocks per compute unit, 128 registers to a lane.  Two samples of 518400 camera rays with
+// prediction: 5.69 ms so, 5.85 ms with 5 blocks for first hits, 6.33 with 6, 5.83 with 3.
+constexpr int kWalkBlocks = 4;
 
 template <int KIND, bool TAB, bool SET, bool DIRECT, int TEAM>
-__global__ void __launch_bounds__(kWalkThreads, walk_blocks(KIND)) k_paths(Medium M, TracerParams tp, PathArgs A)
+__global__ void __launch_bounds__(kWalkThreads, kWalkBlocks) k_paths(Medium M, TracerParams tp, PathArgs A)
 {
     constexpr int W = 4 * TEAM;  // words of a window
     constexpr int kSteps = (int)kMaxSteps;
@@ -1326,24 +1326,30 @@ PathScratch path_scratch(void *ws, int64_t P)
 }
 
 // Waves of a walk: as many as the chip holds at the kernel's registers, or fewer where there
-// are not enough paths; with few paths teams of 16 shorten each path's chain.
+// are not enough paths; with few paths teams of 16 shorten each path's chain.  First hits
+// are one flight to the first collision, so a wave is better off with more rays than with
+// longer windows (two samples of 518400 camera rays with prediction: teams of 4 5.80 ms, of
+// 8 5.96 ms, of 16 6.22 ms); walks with bounces are not (records of 2048 x 256 paths: 47.7,
+// 36.0 and 39 to 44 ms).
 constexpr int64_t kFewPaths = 1 << 14;
-constexpr int kTeam = 8, kTeamFew = 16;
+constexpr int kTeamFew = 16;
+constexpr int team_of(int kind) { return kind == kFirstHits ? 4 : 8; }
 constexpr int kComputeUnits = 256;
 
 template <int KIND, bool TAB, bool SET, bool DIRECT>
 void walk(hipStream_t s, const Medium &M, const TracerParams &tp, PathArgs &A, int64_t paths)
 {
     const bool few = paths <= kFewPaths;
-    const int team = few ? kTeamFew : kTeam, teams = kWalkThreads / team;  // per block
+    const int team = few ? kTeamFew : team_of(KIND), teams = kWalkThreads / team;  // per block
     const int64_t blocks = std::min<int64_t>((paths + teams - 1) / teams,
-                                             kComputeUnits * walk_blocks(KIND));
+                                             kComputeUnits * kWalkBlocks);
     const int64_t per = paths / (blocks * (kWalkThreads / 64) * 4);  // a quarter of a wave's share
     A.grab = (int)std::max<int64_t>(A.head ? 1 : 64 / team, std::min<int64_t>(per, 16));
     if (few)
         k_paths<KIND, TAB, SET, DIRECT, kTeamFew><<<(unsigned)blocks, kWalkThreads, 0, s>>>(M, tp, A);
     else
-        k_paths<KIND, TAB, SET, DIRECT, kTeam><<<(unsigned)blocks, kWalkThreads, 0, s>>>(M, tp, A);
+        k_paths<KIND, TAB, SET, DIRECT, team_of(KIND)>
+            <<<(unsigned)blocks, kWalkThreads, 0, s>>>(M, tp, A);
 }
 
 // One walk per item without sums (first hits, record draws); waves take fixed shares, so the
