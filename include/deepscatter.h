@@ -246,7 +246,8 @@ typedef struct ds_batch ds_batch;
  * offsets[c+1]-1 of the concatenated point arrays (offsets: host, n_clouds + 1
  * non-decreasing values, offsets[0] = 0).  The plan keeps the cloud and network
  * handles (they must outlive it) and starts with the variant ds_predict uses
- * (DS_KERNEL_REGISTER, 4 waves, one workgroup per tile). */
+ * (DS_KERNEL_REGISTER, 4 waves, one workgroup per tile).  With that variant launches of up
+ * to 8192 points run a kernel of their own for few points, with bitwise the same results. */
 ds_status ds_batch_create(ds_ctx *ctx, const ds_net *net, int n_clouds,
                           const ds_cloud *const *clouds, const int64_t *offsets, ds_batch **out);
 ds_status ds_batch_destroy(ds_batch *batch);

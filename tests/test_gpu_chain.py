@@ -132,7 +132,8 @@ def test_loss_and_gradients_at_tile_edges(ctx, K, W, H, B):
 
 
 @pytest.mark.parametrize("K,W,H,P", [
-    (1, 1, 1, 4097), (2, 17, 3, 4096), (2, 33, 2, 4111), (1, 256, 1, 4129), (3, 200, 3, 4113)])
+    (1, 1, 1, 4097), (2, 17, 3, 4096), (2, 33, 2, 4111), (1, 256, 1, 4129), (3, 200, 3, 4113),
+    (16, 256, 8, 4097)])  # the last: the most LDS
 def test_forward_on_both_sides_of_the_row_rule(ctx, K, W, H, P):
     net, theta, z, _ = _case(ctx, K, W, H, P)
     zt = torch.from_numpy(z).cuda()

@@ -34,7 +34,8 @@ def _points(P, amin, h0, n, seed):
 @pytest.mark.parametrize("K,W,H,counts", [
     (1, 1, 1, (1, 0)), (3, 16, 3, (4, 5)), (5, 32, 2, (17, 1006)), (6, 64, 3, (1000, 26)),
     (16, 100, 4, (37, 8155)), (10, 200, 3, (1025, 0)), (4, 256, 1, (333, 692)),
-    (2, 250, 5, (8000, 192)), (2, 176, 3, (8193, 0))])
+    (2, 250, 5, (8000, 192)), (2, 176, 3, (8193, 0)),
+    (16, 256, 8, (1030, 7))])  # the last: the most LDS
 def test_few_points_match_the_register_kernel(ctx, prec, K, W, H, counts):
     n = 24
     amin, h0 = synth.unit_box(n)
