@@ -366,7 +366,7 @@ __device__ V3 around(V3 w, float c, float u)
 // windows per path), teams of 16 39 ms (more idle words at a phase's end); below 2^14 paths
 // teams of 16 win, since there a launch lasts as long as its longest path.
 enum PathKind {
-    kRecordPaths,  // L_i (or L_s) of a record: k_trace_li's estimates
+    kRecordPaths,  // L_i (or L_s) of a record: ds_trace_li's estimates
     kPixelPaths,   // path-traced camera samples
     kFirstHits,    // first collision of a camera ray and its direct light
     kRecordDraws,  // record configurations (Sec. 5.1)
