@@ -470,6 +470,9 @@ def main():
     kname = {ds.DS_KERNEL_REGISTER: "k_fused_reg", ds.DS_KERNEL_PIPELINED: "k_fused",
              ds.DS_KERNEL_WIDE: "k_fused_wide",
              ds.DS_KERNEL_TEAMS: "k_fused_teams"}[tuned["kernel"]] + f"<{mt},{tuned['waves']}>"
+    if tuned["kernel"] == ds.DS_KERNEL_REGISTER and tuned["waves"] == 4 and not tuned["grid"] \
+            and P <= 8192:  # such launches run the kernel for few points
+        kname = f"k_fused_few<{mt},{4 if P <= 1024 else 16}>"
     traffic, traffic_grid = measured_traffic(kname) if args.workload == "paper" else (None, "")
     roofline = {"bound": "mfma", "achieved": round(achieved, 2), "peak": PEAK_BF16_TFLOPS,
                 "unit": "TFLOP/s", "frac": round(achieved / PEAK_BF16_TFLOPS, 4),
