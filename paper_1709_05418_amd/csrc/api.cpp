@@ -47,13 +47,39 @@ bool unit_host(const float *v, float *u)
     return true;
 }
 
+static bool freed(void *p)
+{
+    if (hipFree(p) == hipSuccess)
+        return true;
+    (void)hipGetLastError();
+    return false;
+}
+
 void blocks_free(ds_ctx *ctx)
 {
     std::lock_guard<std::mutex> lock(ctx->blocks_mutex);
-    for (auto &b : ctx->blocks)
-        (void)hipFree(b.first);
-    ctx->blocks.clear();
-    ctx->blocks_bytes = 0;
+    auto &b = ctx->blocks;
+    b.erase(std::remove_if(b.begin(), b.end(),
+                           [&](const std::pair<void *, size_t> &e) {
+                               if (!freed(e.first))
+                                   return false;
+                               ctx->blocks_bytes -= e.second;
+                               return true;
+                           }),
+            b.end());
+    auto &r = ctx->refused;
+    r.erase(std::remove_if(r.begin(), r.end(), freed), r.end());
+}
+
+void block_free(ds_ctx *ctx, void *p)
+{
+    if (!p || freed(p))
+        return;
+    std::lock_guard<std::mutex> lock(ctx->blocks_mutex);
+    try {
+        ctx->refused.push_back(p);
+    } catch (...) {
+    }
 }
 
 void *block_take(ds_ctx *ctx, size_t *bytes)
@@ -87,7 +113,7 @@ void block_give(ds_ctx *ctx, void *p, size_t bytes)
 {
     if (!p)
         return;
-    if (ctx) {
+    {
         std::lock_guard<std::mutex> lock(ctx->blocks_mutex);
         if (ctx->blocks_bytes + bytes <= kBlocksKept) {
             try {
@@ -98,7 +124,7 @@ void block_give(ds_ctx *ctx, void *p, size_t bytes)
             }
         }
     }
-    (void)hipFree(p);
+    block_free(ctx, p);
 }
 
 namespace {
@@ -869,19 +895,26 @@ ds_status ds_cloud_destroy(ds_cloud *c)
 {
     if (!c)
         return DS_OK;
-    // the blocks may go to another cloud: wait for every stream that may still read them, as
-    // freeing them does
+    // the blocks may go to another cloud: wait for every stream that may still read them.  Where
+    // that is refused (while a stream is captured) or fails they are not handed on: hipFree
+    // waits by itself
+    ds_ctx *ctx = c->ctx;
     int dev = -1;
     (void)hipGetDevice(&dev);
-    (void)hipSetDevice(c->ctx->device);
-    (void)hipStreamSynchronize(c->ctx->stream);
-    (void)hipDeviceSynchronize();
+    const bool idle = hipSetDevice(ctx->device) == hipSuccess && hipDeviceSynchronize() == hipSuccess;
+    if (idle) {
+        block_give(ctx, c->block, c->block_bytes);
+        block_give(ctx, c->cells32, c->cells32_bytes);
+        block_give(ctx, c->mu_cells, c->mu_cells_bytes);
+    } else {
+        (void)hipGetLastError();
+        block_free(ctx, c->block);
+        block_free(ctx, c->cells32);
+        block_free(ctx, c->mu_cells);
+    }
+    block_free(ctx, c->tables);
     if (dev >= 0)
         (void)hipSetDevice(dev);
-    block_give(c->ctx, c->block, c->block_bytes);
-    block_give(c->ctx, c->cells32, c->cells32_bytes);
-    block_give(c->ctx, c->mu_cells, c->mu_cells_bytes);
-    (void)hipFree(c->tables);
     delete c;
     return DS_OK;
 }

@@ -65,6 +65,7 @@ struct ds_ctx {
     std::mutex blocks_mutex;
     std::vector<std::pair<void *, size_t>> blocks;
     size_t blocks_bytes = 0;
+    std::vector<void *> refused;  // blocks that could not be freed yet (see block_free)
 };
 
 struct ds_cloud {
@@ -170,10 +171,13 @@ namespace ds {
 // kBlocksKept bytes of its destroyed clouds' blocks and hands them to the next clouds.
 // block_take: a kept block of *bytes .. 1.25 *bytes, else a new one (the kept ones are
 // given back first where memory runs out); *bytes becomes its size; NULL if out of memory.
-// block_give: the caller has synchronised the device.  Safe from several threads.
+// block_give: the caller has synchronised the device.  block_free: for blocks that it could
+// not wait for; one that hipFree refuses (while a stream is captured) is set aside and freed
+// with the kept ones.  Safe from several threads.
 constexpr size_t kBlocksKept = size_t(4) << 30;
 void *block_take(ds_ctx *ctx, size_t *bytes);
 void block_give(ds_ctx *ctx, void *p, size_t bytes);
+void block_free(ds_ctx *ctx, void *p);
 void blocks_free(ds_ctx *ctx);
 
 // ------------------------------------------------------------------ kernels (launchers)
