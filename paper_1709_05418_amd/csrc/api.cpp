@@ -71,6 +71,41 @@ void blocks_free(ds_ctx *ctx)
     r.erase(std::remove_if(r.begin(), r.end(), freed), r.end());
 }
 
+// The process's contexts, whose kept blocks an allocation may need.
+static std::mutex g_contexts_mutex;
+static std::vector<ds_ctx *> g_contexts;
+
+static bool context_add(ds_ctx *ctx)
+{
+    std::lock_guard<std::mutex> lock(g_contexts_mutex);
+    try {
+        g_contexts.push_back(ctx);
+    } catch (...) {
+        return false;
+    }
+    return true;
+}
+
+static void context_remove(ds_ctx *ctx)
+{
+    std::lock_guard<std::mutex> lock(g_contexts_mutex);
+    g_contexts.erase(std::find(g_contexts.begin(), g_contexts.end(), ctx));
+}
+
+hipError_t device_malloc_bytes(void **p, size_t bytes)
+{
+    hipError_t e = hipMalloc(p, bytes);
+    if (e != hipErrorOutOfMemory)
+        return e;
+    (void)hipGetLastError();
+    {
+        std::lock_guard<std::mutex> lock(g_contexts_mutex);
+        for (ds_ctx *c : g_contexts)
+            blocks_free(c);
+    }
+    return hipMalloc(p, bytes);
+}
+
 void block_free(ds_ctx *ctx, void *p)
 {
     if (!p || freed(p))
@@ -102,11 +137,7 @@ void *block_take(ds_ctx *ctx, size_t *bytes)
         }
     }
     void *p = nullptr;
-    if (hipMalloc(&p, *bytes) == hipSuccess)
-        return p;
-    (void)hipGetLastError();
-    blocks_free(ctx);
-    return hipMalloc(&p, *bytes) == hipSuccess ? p : nullptr;
+    return device_malloc(&p, *bytes) == hipSuccess ? p : nullptr;
 }
 
 void block_give(ds_ctx *ctx, void *p, size_t bytes)
@@ -151,7 +182,7 @@ ds_status ensure_ws(ds_ctx *ctx, size_t bytes)
         ctx->ws = nullptr;
         ctx->ws_bytes = 0;
     }
-    DS_HIP(hipMalloc(&ctx->ws, bytes));
+    DS_HIP(device_malloc(&ctx->ws, bytes));
     ctx->ws_bytes = bytes;
     return DS_OK;
 }
@@ -166,7 +197,7 @@ ds_status ensure_ws2(ds_ctx *ctx, size_t bytes)
         ctx->ws2 = nullptr;
         ctx->ws2_bytes = 0;
     }
-    DS_HIP(hipMalloc(&ctx->ws2, bytes));
+    DS_HIP(device_malloc(&ctx->ws2, bytes));
     ctx->ws2_bytes = bytes;
     return DS_OK;
 }
@@ -338,7 +369,7 @@ ds_status train_ws(ds_net *net, int B, ChainArgs &a)
             net->tws = nullptr;
             net->tws_floats = 0;
         }
-        DS_HIP(hipMalloc(&net->tws, need * sizeof(float)));
+        DS_HIP(device_malloc(&net->tws, need * sizeof(float)));
         net->tws_floats = need;
     }
     float *p = net->tws;
@@ -379,7 +410,7 @@ static ds_status mlp_loss_grad(ds_net *net, const float *z, const float *target,
             net->tws = nullptr;
             net->tws_floats = 0;
         }
-        DS_HIP(hipMalloc(&net->tws, need * sizeof(float)));
+        DS_HIP(device_malloc(&net->tws, need * sizeof(float)));
         net->tws_floats = need;
     }
     std::vector<float *> A(L), Y(L);
@@ -580,11 +611,17 @@ ds_status ds_create(int device, void *hip_stream, ds_ctx **out)
     DS_CHECK(c, DS_ERR_OOM, "ds_create: out of host memory");
     c->device = device;
     c->stream = static_cast<hipStream_t>(hip_stream);
-    if (hipMalloc(&c->truncated, sizeof(unsigned long long)) != hipSuccess ||
+    if (device_malloc(&c->truncated, sizeof(unsigned long long)) != hipSuccess ||
         hipMemset(c->truncated, 0, sizeof(unsigned long long)) != hipSuccess) {
         (void)hipFree(c->truncated);
         delete c;
         set_error("ds_create: out of device memory for the tracer counter");
+        return DS_ERR_OOM;
+    }
+    if (!context_add(c)) {
+        (void)hipFree(c->truncated);
+        delete c;
+        set_error("ds_create: out of host memory");
         return DS_ERR_OOM;
     }
     *out = c;
@@ -623,6 +660,7 @@ ds_status ds_destroy(ds_ctx *ctx)
 {
     if (!ctx)
         return DS_OK;
+    context_remove(ctx);
     if (ctx->ws || ctx->ws2)
         (void)hipStreamSynchronize(ctx->stream);
     (void)hipFree(ctx->ws);
@@ -669,7 +707,7 @@ ds_status ds_cloud_create(ds_ctx *ctx, const void *density_dev, ds_dtype dtype, 
         ds_cloud_destroy(c);
         return s;
     };
-    if (hipMalloc(&scratch, cloud_scratch_bytes(n_levels)) != hipSuccess) {
+    if (device_malloc(&scratch, cloud_scratch_bytes(n_levels)) != hipSuccess) {
         set_error("ds_cloud_create: out of device memory for the build's scratch");
         return fail(DS_ERR_OOM);
     }
@@ -797,7 +835,7 @@ ds_status ds_cloud_create(ds_ctx *ctx, const void *density_dev, ds_dtype dtype, 
         fl[k].fast = l.fast ? 1 : 0;
     }
     size_t tb = sizeof(GatherLevel) * K + sizeof(FusedLevel) * K + 64;
-    if (hipMalloc(&c->tables, tb) != hipSuccess) {
+    if (device_malloc(&c->tables, tb) != hipSuccess) {
         set_error("ds_cloud_create: out of device memory for the level tables");
         return fail(DS_ERR_OOM);
     }
@@ -949,8 +987,8 @@ ds_status ds_net_create(ds_ctx *ctx, const ds_net_desc *desc, ds_net **out)
     n->n_params = ds_net_param_count(desc);
     const size_t cb = chain_pack_bytes(n->K, n->W, n->H, false);
     const size_t cb16 = chain_pack_bytes(n->K, n->W, n->H, true);
-    if (hipMalloc(&n->theta, sizeof(float) * n->n_params) != hipSuccess ||
-        hipMalloc(&n->chain, cb) != hipSuccess || hipMalloc(&n->chain16, cb16) != hipSuccess) {
+    if (device_malloc(&n->theta, sizeof(float) * n->n_params) != hipSuccess ||
+        device_malloc(&n->chain, cb) != hipSuccess || device_malloc(&n->chain16, cb16) != hipSuccess) {
         ds_net_destroy(n);
         set_error("ds_net_create: out of device memory");
         return DS_ERR_OOM;
@@ -1002,7 +1040,7 @@ ds_status ds_net_create_mlp(ds_ctx *ctx, int32_t K, int32_t n_layers, const int3
         n->W = widths[l] > n->W ? widths[l] : n->W;
     }
     n->n_params = np;
-    if (hipMalloc(&n->theta, sizeof(float) * np) != hipSuccess) {
+    if (device_malloc(&n->theta, sizeof(float) * np) != hipSuccess) {
         delete n;
         set_error("ds_net_create_mlp: out of device memory");
         return DS_ERR_OOM;
@@ -1380,7 +1418,7 @@ ds_status ds_batch_set_order(ds_batch *b, int32_t order)
                                  (size_t)order_buckets(b->n), (size_t)order_sums(b->n)};
         int32_t **bufs[4] = {&b->perm, &b->slot, &b->counts, &b->sums};
         for (int i = 0; i < 4; ++i) {
-            hipError_t e = hipMalloc((void **)bufs[i], sizes[i] * sizeof(int32_t));
+            hipError_t e = device_malloc((void **)bufs[i], sizes[i] * sizeof(int32_t));
             if (e != hipSuccess) {
                 *bufs[i] = nullptr;
                 batch_free_order(b);
@@ -1616,10 +1654,10 @@ ds_status ds_net_quantize(ds_ctx *ctx, ds_net *net, const ds_cloud *cloud, ds_pr
     // calibration: the FP32 plain form, recording the largest activation of every layer
     unsigned *amax = nullptr;
     float *out = nullptr;
-    DS_CHECK(hipMalloc(&amax, sizeof(unsigned) * na) == hipSuccess, DS_ERR_OOM,
+    DS_CHECK(device_malloc(&amax, sizeof(unsigned) * na) == hipSuccess, DS_ERR_OOM,
              "ds_net_quantize: out of device memory");
     ds_status st = DS_OK;
-    if (hipMalloc(&out, sizeof(float) * (size_t)n_calib) != hipSuccess) {
+    if (device_malloc(&out, sizeof(float) * (size_t)n_calib) != hipSuccess) {
         st = DS_ERR_OOM;
         set_error("ds_net_quantize: out of device memory");
     }
@@ -1690,9 +1728,9 @@ ds_status ds_adam_create(ds_net *net, float lr, float beta1, float beta2, float 
     a->b2 = beta2;
     a->eps = eps;
     const size_t n = (size_t)net->n_params;
-    if (hipMalloc(&a->m, n * 4) != hipSuccess || hipMalloc(&a->v, n * 4) != hipSuccess ||
-        hipMalloc(&a->grad, n * 4) != hipSuccess || hipMalloc(&a->steps, 8) != hipSuccess ||
-        hipMalloc(&a->state, 16) != hipSuccess) {
+    if (device_malloc(&a->m, n * 4) != hipSuccess || device_malloc(&a->v, n * 4) != hipSuccess ||
+        device_malloc(&a->grad, n * 4) != hipSuccess || device_malloc(&a->steps, 8) != hipSuccess ||
+        device_malloc(&a->state, 16) != hipSuccess) {
         ds_adam_destroy(a);
         set_error("ds_adam_create: out of device memory");
         return DS_ERR_OOM;
@@ -2310,7 +2348,7 @@ ds_status ds_phase_create(ds_ctx *ctx, int32_t n, const double *p, double chop_d
     ph->mean_cos = g;
     hipError_t e = hipSetDevice(ctx->device);
     if (e == hipSuccess)
-        e = hipMalloc(&ph->p, sizeof(float) * 2 * (size_t)n);
+        e = device_malloc(&ph->p, sizeof(float) * 2 * (size_t)n);
     if (e == hipSuccess)
         e = hipMemcpy(ph->p, hf.data(), sizeof(float) * 2 * (size_t)n, hipMemcpyHostToDevice);
     if (e != hipSuccess) {
@@ -2374,9 +2412,9 @@ ds_status ds_lights_create(ds_ctx *ctx, int32_t m, const float *dirs, const doub
     L->m = m;
     hipError_t e = hipSetDevice(ctx->device);
     if (e == hipSuccess)
-        e = hipMalloc(&L->dw, sizeof(float4) * (size_t)m);
+        e = device_malloc(&L->dw, sizeof(float4) * (size_t)m);
     if (e == hipSuccess)
-        e = hipMalloc(&L->thr, sizeof(uint32_t) * (size_t)m);
+        e = device_malloc(&L->thr, sizeof(uint32_t) * (size_t)m);
     if (e == hipSuccess)
         e = hipMemcpy(L->dw, dw.data(), sizeof(float4) * (size_t)m, hipMemcpyHostToDevice);
     if (e == hipSuccess)

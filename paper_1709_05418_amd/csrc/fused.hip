@@ -2328,16 +2328,16 @@ ds_status fused_prepare(ds_net *net)
     const int64_t nf = (int64_t)fmap.size(), nv = (int64_t)vmap.size();
     // zeroed tail: the kernel's branch-free staging may read past the last chunk
     const size_t fbytes = (size_t)nf * 2 + kFragPad * 16;
-    DS_CHECK(hipMalloc(&net->frag_bf16, fbytes) == hipSuccess, DS_ERR_OOM,
+    DS_CHECK(device_malloc(&net->frag_bf16, fbytes) == hipSuccess, DS_ERR_OOM,
              "out of device memory for the packed weights");
     DS_HIP(hipMemset(net->frag_bf16, 0, fbytes));
     net->frag_count = nf / 8;
-    DS_CHECK(hipMalloc(&net->vec, (size_t)nv * 4) == hipSuccess, DS_ERR_OOM,
+    DS_CHECK(device_malloc(&net->vec, (size_t)nv * 4) == hipSuccess, DS_ERR_OOM,
              "out of device memory for the packed biases");
     net->vec_count = nv;
-    DS_CHECK(hipMalloc(&net->fmap, (size_t)nf * 4) == hipSuccess, DS_ERR_OOM,
+    DS_CHECK(device_malloc(&net->fmap, (size_t)nf * 4) == hipSuccess, DS_ERR_OOM,
              "out of device memory for the packing map");
-    DS_CHECK(hipMalloc(&net->vmap, (size_t)nv * 4) == hipSuccess, DS_ERR_OOM,
+    DS_CHECK(device_malloc(&net->vmap, (size_t)nv * 4) == hipSuccess, DS_ERR_OOM,
              "out of device memory for the packing map");
     DS_HIP(hipMemcpy(net->fmap, fmap.data(), (size_t)nf * 4, hipMemcpyHostToDevice));
     DS_HIP(hipMemcpy(net->vmap, vmap.data(), (size_t)nv * 4, hipMemcpyHostToDevice));
@@ -2614,9 +2614,9 @@ ds_status fused_quantize_fp8(ds_net *net, const float *th, const float *act_amax
     vec[wl + WP] = th[pb.hb[H - 1]];
 
     if (!net->frag_fp8) {
-        DS_CHECK(hipMalloc(&net->frag_fp8, fr.size() * sizeof(uint4)) == hipSuccess, DS_ERR_OOM,
+        DS_CHECK(device_malloc(&net->frag_fp8, fr.size() * sizeof(uint4)) == hipSuccess, DS_ERR_OOM,
                  "out of device memory for the FP8 weights");
-        DS_CHECK(hipMalloc(&net->vec8, vec.size() * sizeof(float)) == hipSuccess, DS_ERR_OOM,
+        DS_CHECK(device_malloc(&net->vec8, vec.size() * sizeof(float)) == hipSuccess, DS_ERR_OOM,
                  "out of device memory for the FP8 vectors");
         net->frag8_count = (int64_t)fr.size();
     }

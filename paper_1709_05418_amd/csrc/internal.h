@@ -169,12 +169,19 @@ namespace ds {
 // 0.25 ms a block at best, and 5 to 20 ms, now and then a second, once the driver has to
 // wipe and remap them (measured over 300 loads of a 256^3 cloud), so a context keeps up to
 // kBlocksKept bytes of its destroyed clouds' blocks and hands them to the next clouds.
-// block_take: a kept block of *bytes .. 1.25 *bytes, else a new one (the kept ones are
-// given back first where memory runs out); *bytes becomes its size; NULL if out of memory.
+// device_malloc: hipMalloc for all of the library's allocations; where memory runs out the kept
+// blocks of the process's contexts are given back first.
+// block_take: a kept block of *bytes .. 1.25 *bytes, else a new one; *bytes becomes its size;
+// NULL if out of memory.
 // block_give: the caller has synchronised the device.  block_free: for blocks that it could
 // not wait for; one that hipFree refuses (while a stream is captured) is set aside and freed
 // with the kept ones.  Safe from several threads.
 constexpr size_t kBlocksKept = size_t(4) << 30;
+hipError_t device_malloc_bytes(void **p, size_t bytes);
+template <class T> hipError_t device_malloc(T **p, size_t bytes)
+{
+    return device_malloc_bytes(reinterpret_cast<void **>(p), bytes);
+}
 void *block_take(ds_ctx *ctx, size_t *bytes);
 void block_give(ds_ctx *ctx, void *p, size_t bytes);
 void block_free(ds_ctx *ctx, void *p);

@@ -103,3 +103,59 @@ def test_a_block_that_could_be_neither_waited_for_nor_freed_is_set_aside(run):
     L.ds_cloud_destroy(b); L.ds_destroy(ctx)
     assert F.fake_live_bytes() == 0   # and not lost
     """)
+
+
+# What a call allocates: a network (parameters, packed copies), its fragments, Adam's moments,
+# workspaces, a batch's order buffers, a light set, a phase table
+CALLS = {
+    "net": "lambda: L.ds_net_create(ctx, C.byref(ds._NetDesc(10, 200, 3)), C.byref(out))",
+    "mlp": "lambda: L.ds_net_create_mlp(ctx, 10, 2, (C.c_int32 * 2)(200, 1), C.byref(out))",
+    "params": "lambda: L.ds_net_set_params(net, theta, n)",
+    "adam": "lambda: L.ds_adam_create(net, C.c_float(1e-3), C.c_float(.9), C.c_float(.999), C.c_float(1e-8), C.byref(out))",
+    "gradient": "lambda: L.ds_loss_grad(net, density, density, 512, density, density)",
+    "trace": "lambda: L.ds_trace_li(ctx, keep, C.byref(prm), density, density, density, C.c_int64(4096), 1024, C.c_uint64(1), density, None)",
+    "predict": "lambda: L.ds_predict(ctx, keep, net, 0, density, density, density, C.c_int64(4096), density, None, None)",
+    "lights": "lambda: L.ds_lights_create(ctx, 65536, dirs, irr, C.byref(out))",
+    "cloud": "lambda: L.ds_cloud_create(ctx, density, 0, 64, 64, 64, C.c_float(1), (C.c_float * 3)(0, 0, 0), C.c_float(1 / 64), 2, None, 2, C.byref(out))",
+    "context": "lambda: L.ds_create(0, None, C.byref(out))",
+}
+
+
+@pytest.mark.parametrize("owner", ["same", "other"])
+@pytest.mark.parametrize("call", CALLS)
+def test_kept_blocks_make_room_for_any_call(run, call, owner):
+    # the memory that the call needs is held by a destroyed cloud's block alone
+    run(f"""
+    ctx = context()
+    other = context()
+    out = C.c_void_p()
+    net = C.c_void_p()
+    prm = ds.TracerParams(0.9, 0.85, 1.0)
+    assert L.ds_net_create(ctx, C.byref(ds._NetDesc(2, 64, 3)), C.byref(net)) == 0
+    n = ds.ds_net_param_count(2, 64, 3)
+    theta = (C.c_float * n)()
+    import numpy as np
+    d3 = np.ones((65536, 3), np.float32); e1 = np.ones(65536)
+    dirs, irr = C.c_void_p(d3.ctypes.data), C.c_void_p(e1.ctypes.data)
+    keep = cloud(ctx, 8)
+    owner = dict(same=ctx, other=other)[{owner!r}]
+    a = cloud(owner, 150)
+    L.ds_cloud_destroy(a)
+    F.fake_limit(F.fake_live_bytes())
+    F.fake_count(0)
+    st = ({CALLS[call]})()
+    assert st == 0, ds.ds_last_error()
+    assert F.fake_mallocs() > 0 and F.fake_frees() > 0
+    # the refused allocation leaves no error behind
+    assert L.ds_synchronize(ctx) == 0 and F.hipGetLastError() == 0
+    """)
+
+
+def test_a_call_that_does_not_fit_still_says_so(run):
+    run("""
+    ctx = context()
+    out = C.c_void_p()
+    F.fake_limit(F.fake_live_bytes() + MIB)
+    assert L.ds_net_create(ctx, C.byref(ds._NetDesc(10, 200, 3)), C.byref(out)) == -2
+    assert "memory" in ds.ds_last_error()
+    """)
