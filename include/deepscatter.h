@@ -116,8 +116,8 @@ ds_status ds_cloud_info(const ds_cloud *cloud, double *mean_mu_t, int *n_levels,
 /* Copy mip level `level` (float32, [nz][ny][nx]) into caller device memory. */
 ds_status ds_cloud_level(ds_ctx *ctx, const ds_cloud *cloud, int level, float *dst_dev);
 /* Waits for the device, then releases the cloud.  The context keeps up to 4 GiB of its
- * destroyed clouds' device memory for the next clouds until ds_destroy, or until an
- * allocation of the library would fail without it. */
+ * destroyed clouds' device memory for the next clouds (the most recent ones) until ds_destroy,
+ * or until an allocation of the library would fail without it. */
 ds_status ds_cloud_destroy(ds_cloud *cloud);
 
 /* ---------------------------------------------------------------- network (Sec. 4.3) */

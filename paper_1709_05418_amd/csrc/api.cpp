@@ -144,11 +144,16 @@ void block_give(ds_ctx *ctx, void *p, size_t bytes)
 {
     if (!p)
         return;
-    {
+    if (bytes <= kBlocksKept) {
         std::lock_guard<std::mutex> lock(ctx->blocks_mutex);
+        auto &b = ctx->blocks;
+        while (ctx->blocks_bytes + bytes > kBlocksKept && freed(b.front().first)) {
+            ctx->blocks_bytes -= b.front().second;
+            b.erase(b.begin());
+        }
         if (ctx->blocks_bytes + bytes <= kBlocksKept) {
             try {
-                ctx->blocks.emplace_back(p, bytes);
+                b.emplace_back(p, bytes);
                 ctx->blocks_bytes += bytes;
                 return;
             } catch (...) {

@@ -173,9 +173,9 @@ namespace ds {
 // blocks of the process's contexts are given back first.
 // block_take: a kept block of *bytes .. 1.25 *bytes, else a new one; *bytes becomes its size;
 // NULL if out of memory.
-// block_give: the caller has synchronised the device.  block_free: for blocks that it could
-// not wait for; one that hipFree refuses (while a stream is captured) is set aside and freed
-// with the kept ones.  Safe from several threads.
+// block_give: the caller has synchronised the device; the blocks kept longest make way.
+// block_free: for blocks that it could not wait for; one that hipFree refuses (while a stream
+// is captured) is set aside and freed with the kept ones.  Safe from several threads.
 constexpr size_t kBlocksKept = size_t(4) << 30;
 hipError_t device_malloc_bytes(void **p, size_t bytes);
 template <class T> hipError_t device_malloc(T **p, size_t bytes)

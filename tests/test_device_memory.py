@@ -159,3 +159,32 @@ def test_a_call_that_does_not_fit_still_says_so(run):
     assert L.ds_net_create(ctx, C.byref(ds._NetDesc(10, 200, 3)), C.byref(out)) == -2
     assert "memory" in ds.ds_last_error()
     """)
+
+
+def test_old_blocks_make_way_for_the_sizes_in_use(run):
+    # once the list was full of blocks that fit no cloud, no new block entered it
+    run("""
+    ctx = context()
+    start = F.fake_live_bytes()
+    held = lambda: F.fake_live_bytes() - start
+    for n in (200, 230, 260, 290, 320, 350, 380, 410, 440):   # no two within a quarter
+        L.ds_cloud_destroy(cloud(ctx, n))
+        assert held() <= (4 << 30) + MIB
+    assert held() > 1 << 30
+    F.fake_count(4 * MIB)
+    L.ds_cloud_destroy(cloud(ctx, 470))      # 3.9 GB
+    assert F.fake_mallocs() == 1 and held() <= (4 << 30) + MIB
+    L.ds_cloud_destroy(cloud(ctx, 470))
+    assert F.fake_mallocs() == 1             # the same block again
+    # the oldest go first: a small block that was used last stays
+    L.ds_cloud_destroy(cloud(ctx, 100))
+    F.fake_count(4 * MIB)
+    L.ds_cloud_destroy(cloud(ctx, 100))
+    assert F.fake_mallocs() == 0
+    # a block larger than the bound is not kept
+    F.fake_count(1 << 32)
+    L.ds_cloud_destroy(cloud(ctx, 700))
+    assert F.fake_mallocs() == 1 and F.fake_frees() == 1
+    L.ds_destroy(ctx)
+    assert F.fake_live_bytes() <= start
+    """)
