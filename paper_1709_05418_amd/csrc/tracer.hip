@@ -6,6 +6,7 @@
 #include <math.h>
 
 #include "internal.h"
+#include "stream.h"
 
 namespace ds {
 namespace {
@@ -13,29 +14,7 @@ namespace {
 constexpr int kPaths = 64;                  // paths per partial sum of a record
 constexpr int64_t kMaxSteps = 1ll << 26;    // hard bound on tentative collisions per path
 
-// ------------------------------------------------------------------ Philox4x32-10
-// Counter-based generator of Salmon et al. (SC'11): 10 rounds of two 32x32->64-bit
-// multiplications mixing the four counter words, with a Weyl-sequence key schedule.
-__device__ __forceinline__ void philox(uint32_t a, uint32_t b, uint32_t x0, uint32_t x1,
-                                       uint32_t x2, uint32_t x3, uint32_t (&out)[4])
-{
-#pragma unroll
-    for (int r = 0; r < 10; ++r) {
-        const uint64_t m0 = (uint64_t)0xD2511F53u * x0, m1 = (uint64_t)0xCD9E8D57u * x2;
-        const uint32_t y0 = (uint32_t)(m1 >> 32) ^ x1 ^ a, y2 = (uint32_t)(m0 >> 32) ^ x3 ^ b;
-        x0 = y0;
-        x1 = (uint32_t)m1;
-        x2 = y2;
-        x3 = (uint32_t)m0;
-        a += 0x9E3779B9u;
-        b += 0xBB67AE85u;
-    }
-    out[0] = x0;
-    out[1] = x1;
-    out[2] = x2;
-    out[3] = x3;
-}
-
+// ------------------------------------------------------------------ random words
 struct Rng {
     uint32_t k0, k1;        // key = seed
     uint32_t c0, c1, c2, c3; // counter = (stream id lo, hi, block, 0)
@@ -365,13 +344,6 @@ __device__ V3 around(V3 w, float c, float u)
 // 0.45 ms.  The vector ALUs issue in 80 % of the cycles.  Teams of 4 take 48 ms (more
 // windows per path), teams of 16 39 ms (more idle words at a phase's end); below 2^14 paths
 // teams of 16 win, since there a launch lasts as long as its longest path.
-enum PathKind {
-    kRecordPaths,  // L_i (or L_s) of a record: ds_trace_li's estimates
-    kPixelPaths,   // path-traced camera samples
-    kFirstHits,    // first collision of a camera ray and its direct light
-    kRecordDraws,  // record configurations (Sec. 5.1)
-};
-
 struct PathArgs {
     const float *a, *b, *light;  // records: position, view, light; rays: origin, direction
     V3 wl;                       // the light of camera rays
@@ -443,7 +415,8 @@ __global__ void __launch_bounds__(kWalkThreads, kWalkBlocks) k_paths(Medium M, T
     uint32_t q0 = 0, q1 = 0;
 
     int phase = kNew, j = 0, steps = 0;
-    uint32_t q = 0, id0 = 0, id1 = 0, item = 0;
+    WordPos<KIND> q = 0;
+    uint32_t id0 = 0, id1 = 0, item = 0;
     int64_t rec = 0;
     V3 p = v3(0, 0, 0), d = p, wprev = p, wh = p, wl = p;
     float t = 0.f, t1 = 0.f, T = 1.f, wgt = 0.f, sum = 0.f, direct = 0.f;
@@ -591,11 +564,11 @@ __global__ void __launch_bounds__(kWalkThreads, kWalkBlocks) k_paths(Medium M, T
 
         // ---- the window: words [q & ~3, q & ~3 + W) of the team's stream, four per lane
         uint32_t b[4];
-        philox((uint32_t)A.seed, (uint32_t)(A.seed >> 32), id0, id1, (q >> 2) + (uint32_t)i, 0, b);
+        stream_block(A.seed, id0, id1, (q >> 2) + (uint32_t)i, b);
 #pragma unroll
         for (int c = 0; c < 4; ++c)
             b[c] >>= 8;
-        const uint32_t qa = q & ~3u;
+        const WordPos<KIND> qa = q & ~(WordPos<KIND>)3;
         int x = (int)(q & 3u);  // cursor: first unread word of the window
         auto word = [&]() {     // a team-uniform read of the next word
             const int w = x++;
