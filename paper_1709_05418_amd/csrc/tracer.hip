@@ -122,7 +122,7 @@ struct Medium {
     unsigned long long *truncated;  // paths stopped at kMaxSteps (the context's counter)
     // Occupied bricks (2^occ_s cells per axis) as bits, brick (i, j, k) at bit
     // i + bx (j + by k); a clear bit says that every cell of the brick is zero.  Entry
-    // occ_words is 1 if some extinction is not finite.
+    // occ_words is 1 if a transmittance factor 1 - mu / maj may not be finite.
     const uint32_t *occ;
     int occ_s, bx, by, occ_words;
 };
@@ -904,9 +904,14 @@ __global__ void __launch_bounds__(kPaths) k_path_sums(const double *val, const i
 
 // Bits of the occupied bricks (see Medium), one wave per brick: brick (i, j, k) holds the
 // cells whose corners are the voxels [i 2^s - 1, (i + 1) 2^s - 1] per axis.
+// wild: an extinction that is not finite, or so large (below zero) that it or its ratio to the
+// majorant overflows on the way from the corners to the factor (bound: a fourth of what FP32
+// holds).
 __global__ void __launch_bounds__(256) k_occupied(const float *mu, int nx, int ny, int nz, int s,
-                                                  int bx, int by, int bz, int words, uint32_t *occ)
+                                                  int bx, int by, int bz, int words, float maj,
+                                                  uint32_t *occ)
 {
+    constexpr float kTame = 8e37f;
     const int64_t br = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (br >= (int64_t)bx * by * bz)
         return;
@@ -919,7 +924,7 @@ __global__ void __launch_bounds__(256) k_occupied(const float *mu, int nx, int n
         if (x >= 0 && y >= 0 && z >= 0 && x < nx && y < ny && z < nz) {
             const float m = mu[((int64_t)z * ny + y) * nx + x];
             on = on || m != 0.f;
-            wild = wild || !isfinite(m);
+            wild = wild || !(fabsf(m) <= kTame && fabsf(m) * (1.f / maj) <= kTame);
         }
     }
     if (__any(on) && lane == 0)
@@ -1212,7 +1217,7 @@ ds_status medium_cells(hipStream_t s, const ds_cloud *c)
         st = tracer_zero(s, reinterpret_cast<double *>(occ), occ64);
     if (!st) {
         k_occupied<<<(unsigned)(((int64_t)b.bx * b.by * b.bz + 3) / 4), 256, 0, s>>>(
-            c->mu, c->nx, c->ny, c->nz, b.s, b.bx, b.by, b.bz, b.words, occ);
+            c->mu, c->nx, c->ny, c->nz, b.s, b.bx, b.by, b.bz, b.words, c->majorant, occ);
         if (hipError_t e = hipGetLastError())
             st = hip_fail(e, "occupied bricks");
     }
