@@ -1,7 +1,7 @@
 // Monte Carlo transport in the cloud (Sec. 3.2 Eq. (1), Sec. 4, Sec. 4.4, Sec. 5.1):
 // delta tracking against a global majorant, ratio-tracked transmittance toward the
 // light, Henyey-Greenstein scattering, absorption by Russian roulette.  A path is walked
-// by a team of lanes (k_paths); per-record sums of the path estimates are accumulated in
+// by a team of lanes (k_paths), a short one by one thread; per-record sums of the path estimates are accumulated in
 // FP64 and reduced in a fixed order, so results are reproducible bit for bit.
 #include <math.h>
 
@@ -349,10 +349,11 @@ struct PathArgs {
     V3 wl;                       // the light of camera rays
     const int32_t *list;         // active items' records (relative to rec0), NULL: all
     const int32_t *n_list;       // device count of the list
-    uint32_t *head;              // queue head; NULL: waves take fixed shares
+    uint32_t *head;              // heads of the queues of items; NULL: waves take fixed shares
     int64_t rec0;                // first record of the list (or of this launch)
     uint32_t slot0, n;           // first item of this launch, its items (at most)
     int spp, s0, grab;
+    uint32_t queues;
     uint64_t seed, sample;
     double *val;                 // one value per path
     float *pos, *view, *light_out, *direct;
@@ -384,6 +385,13 @@ template <int TEAM> __device__ __forceinline__ int team_min(int v)
     return v;
 }
 
+// The items of a launch lie in A.queues queues; a wave takes from its block's until that is empty,
+// then from the others.  With one counter for all, the 4096 waves of a full launch waited for one
+// another's atomics: 64000 paths of a few collisions 222 us, with 32 queues 83 us; 320000 paths
+// 312 and 143 us.  Small launches keep one queue to 16 blocks, as a wave looks at every queue
+// before it ends.
+constexpr uint32_t kQueues = 32, kQueueStride = 32;
+
 constexpr int kWalkThreads = 256;
 constexpr int kOccWords = 2048;  // brick bits in LDS: at most 65536 bricks
 
@@ -410,9 +418,13 @@ __global__ void __launch_bounds__(kWalkThreads, kWalkBlocks) k_paths(Medium M, T
 
     const int lane = threadIdx.x & 63, i = lane & (TEAM - 1), lead = lane & ~(TEAM - 1);
     const uint32_t waves = gridDim.x * (kWalkThreads / 64);
-    // the wave's share of the queue: items q0 .. q1 - 1
+    // the wave's items: q0 .. q1 - 1; the queue it takes from
     uint32_t share = (blockIdx.x * (kWalkThreads / 64) + (threadIdx.x >> 6)) * (uint32_t)A.grab;
-    uint32_t q0 = 0, q1 = 0;
+    uint32_t q0 = 0, q1 = 0, queue = blockIdx.x % A.queues;
+    bool more = true;
+    constexpr bool kQueued = KIND == kRecordPaths || KIND == kPixelPaths;
+    const uint32_t per = kQueued ? (total + A.queues - 1) / A.queues : 0;  // items of a queue
+    auto items_of = [&](uint32_t k) { return k * per < total ? min(per, total - k * per) : 0; };
 
     int phase = kNew, j = 0, steps = 0;
     WordPos<KIND> q = 0;
@@ -473,7 +485,7 @@ __global__ void __launch_bounds__(kWalkThreads, kWalkBlocks) k_paths(Medium M, T
             steps = 0;
             phase = kBounce;
         } else {
-            sum += wgt * Tr * tp.irradiance;
+            sum = fmaf(wgt * Tr, tp.irradiance, sum);
             wprev = wh;
             phase = kBounce;
         }
@@ -491,28 +503,47 @@ __global__ void __launch_bounds__(kWalkThreads, kWalkBlocks) k_paths(Medium M, T
             const uint32_t n = (uint32_t)__popcll(idle), have = q1 - q0;
             const uint32_t rank = (uint32_t)__popcll(idle & ((1ull << lead) - 1));
             uint32_t next = q0 + rank;
+            bool got = rank < have;
             if (n > have) {
                 const uint32_t take = max((uint32_t)A.grab, n - have);
-                uint32_t base;
-                if (A.head) {
-                    base = 0;
-                    if (lane == 0)
-                        base = atomicAdd(A.head, take);
-                    base = __builtin_amdgcn_readfirstlane(base);
-                } else {
-                    base = share;
-                    share += waves * (uint32_t)A.grab;
+                uint32_t base = 0, avail = 0;
+                while (more && avail == 0) {
+                    if constexpr (kQueued) {
+                        if (lane == 0)
+                            base = atomicAdd(A.head + queue * kQueueStride, take);
+                        base = __builtin_amdgcn_readfirstlane(base);
+                        const uint32_t len = items_of(queue);
+                        avail = base < len ? min(take, len - base) : 0;
+                        base += queue * per;
+                        if (avail == 0) {  // on to the next queue that is not empty
+                            const uint32_t l = min((uint32_t)lane, A.queues - 1);
+                            const uint64_t open = __ballot(
+                                __hip_atomic_load(A.head + l * kQueueStride, __ATOMIC_RELAXED,
+                                                  __HIP_MEMORY_SCOPE_AGENT) < items_of(l));
+                            const uint64_t after = open & (~0ull << queue);
+                            more = open != 0;
+                            queue = more ? __builtin_ctzll(after ? after : open) : 0;
+                        }
+                    } else {
+                        base = share;
+                        avail = base < total ? min(take, total - base) : 0;
+                        share += waves * (uint32_t)A.grab;
+                        more = avail != 0;
+                    }
                 }
-                if (rank >= have)
+                if (rank >= have && rank - have < avail) {
                     next = base + (rank - have);
-                q0 = base + (n - have);
-                q1 = base + take;
+                    got = true;
+                }
+                q0 = base + min(n - have, avail);
+                q1 = base + avail;
             } else {
                 q0 += n;
             }
             if (phase == kNew) {
-                if (next >= total) {
-                    phase = kDone;
+                if (!got) {
+                    if (!more)
+                        phase = kDone;
                 } else {
                     item = next;
                     const uint32_t slot = item / (uint32_t)A.spp, s = item - slot * (uint32_t)A.spp;
@@ -828,6 +859,262 @@ __global__ void __launch_bounds__(kWalkThreads, kWalkBlocks) k_paths(Medium M, T
     }
 }
 
+// Launch geometry of the per-record sums: a wave holds kPaths / seg records, each owning
+// seg consecutive lanes (seg a power of two); records with more than kPaths paths have
+// nblk partial sums (then seg = kPaths), which k_finish_sums adds in order.
+struct Split {
+    int seg, nblk;
+};
+
+// ------------------------------------------------------------------ one path per thread
+// For short paths (serial_paths, serial_first_hits, serial_draws say which): no windows drawn for a
+// flight or two, no list, no stored path values, one launch and the sums' instead of four.  The
+// same words in the same order, so bitwise the walker's estimates.  320000 paths in a cloud of
+// two mean free paths: 62 us (teams 178), 1024^2 camera rays on a 64^3 cloud of 60: 147 us (329).
+// One path estimate of the indirect in-scattered radiance at x toward w
+// (directional light: next-event estimation at every collision; uniform
+// environment: the radiance of escaping paths after at least one collision, or
+// any escape when count_uncollided).
+template <bool TAB, bool SET>
+__device__ float li_path(const Medium &M, const TracerParams &tp, V3 x, V3 w, V3 wl,
+                         bool count_uncollided, Rng &r)
+{
+    V3 wprev = w, p = x;
+    float sum = 0.f;
+    int64_t steps = 0;
+    for (int j = 1;; ++j) {
+        if ((tp.max_interactions > 0 && j > tp.max_interactions) || steps >= kMaxSteps)
+            break;
+        const float c = phase_sample<TAB>(tp, r.u());
+        const V3 wh = around(wprev, c, r.u());
+        V3 xn;
+        if (!delta_track(M, p, neg(wh), r, xn, steps)) {
+            if (tp.light_mode == 1 && (j > 1 || count_uncollided))
+                sum += tp.irradiance;
+            break;
+        }
+        p = xn;
+        if (r.u() >= tp.albedo)
+            break;
+        if constexpr (SET) {
+            const float4 lw = tp.set_dw[set_pick(tp, r.bits24())];
+            const V3 lj = v3(lw.x, lw.y, lw.z);
+            sum = fmaf(lw.w * phase_eval<TAB>(tp, false, -dot(wh, lj)) *
+                           ratio_track(M, p, lj, r, steps),
+                       tp.irradiance, sum);
+        } else if (tp.light_mode == 0) {
+            sum = fmaf(phase_eval<TAB>(tp, false, -dot(wh, wl)) * ratio_track(M, p, wl, r, steps),
+                       tp.irradiance, sum);
+        }
+        wprev = wh;
+    }
+    return sum;
+}
+
+// Deterministic segmented reduction of (sum, sum of squares) in FP64: thread
+// t of each segment ends holding nothing; the segment leader writes the totals.
+__device__ void segment_sums(double s1, double s2, int seg, bool write, double *out)
+{
+    __shared__ double a[kPaths], b[kPaths];
+    const int t = threadIdx.x;
+    a[t] = s1;
+    b[t] = s2;
+    __syncthreads();
+    for (int w = seg >> 1; w > 0; w >>= 1) {
+        if ((t & (seg - 1)) < w) {
+            a[t] += a[t + w];
+            b[t] += b[t + w];
+        }
+        __syncthreads();
+    }
+    if (write && (t & (seg - 1)) == 0) {
+        out[0] = a[t];
+        out[1] = b[t];
+    }
+}
+
+// One record estimate: L_i, or with tp.include_direct all in-scattered radiance L_s =
+// L_d + L_i (directional light: the direct term by ratio tracking, drawn before the path;
+// uniform environment: uncollided light counted too).
+template <bool TAB, bool DIRECT>
+__device__ float record_path(const Medium &M, const TracerParams &tp, V3 x, V3 w, V3 wl, Rng &r)
+{
+    if constexpr (!DIRECT) {
+        return li_path<TAB, false>(M, tp, x, w, wl, false, r);
+    } else {
+        if (tp.light_mode == 1)
+            return li_path<TAB, false>(M, tp, x, w, wl, true, r);
+        int64_t steps = 0;
+        const float d =
+            phase_eval<TAB>(tp, false, -dot_direct(w, wl)) * ratio_track(M, x, wl, r, steps);
+        return fmaf(d, tp.irradiance, li_path<TAB, false>(M, tp, x, w, wl, false, r));
+    }
+}
+
+// Paths s0 .. s0 + spp - 1 of every record (path s on stream id rec * 2^20 + s).
+template <bool TAB, bool DIRECT>
+__global__ void __launch_bounds__(kPaths) k_trace_li(Medium M, TracerParams tp, const float *pos,
+                                                     const float *view, const float *light,
+                                                     int64_t P, int s0, int spp, Split sp,
+                                                     uint64_t seed, const uint8_t *mask,
+                                                     uint8_t mask_bits, double *partial)
+{
+    const int64_t group = blockIdx.x / sp.nblk;
+    const int blk = blockIdx.x % sp.nblk;
+    const int64_t rec = group * (kPaths / sp.seg) + threadIdx.x / sp.seg;
+    const int s = blk * sp.seg + (threadIdx.x & (sp.seg - 1));
+    double e = 0.0;
+    V3 w, wl;
+    const bool wanted = rec < P && (!mask || (mask[rec] & mask_bits) == mask_bits);
+    if (wanted && s < spp && unit(view + 3 * rec, w) && unit(light + 3 * rec, wl)) {
+        const V3 x = v3(pos[3 * rec], pos[3 * rec + 1], pos[3 * rec + 2]);
+        Rng r;
+        r.init(seed, ((uint64_t)rec << 20) + (uint64_t)(s0 + s));
+        e = (double)record_path<TAB, DIRECT>(M, tp, x, w, wl, r);
+    }
+    segment_sums(e, e * e, sp.seg, rec < P, partial + 2 * ((size_t)rec * sp.nblk + blk));
+}
+
+// Record configurations (Sec. 5.1): direction d uniform on the sphere, origin
+// uniform over the bounding sphere's cross-section orthogonal to d, a free flight
+// along d into the cloud, retried on escape; view = -d, light uniform.
+__global__ void __launch_bounds__(256) k_sample_records(Medium M, int64_t N, uint64_t seed,
+                                                        float *pos, float *view, float *light,
+                                                        int32_t *attempts)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= N)
+        return;
+    const V3 c = v3(0.5f * (M.amin.x + M.amax.x), 0.5f * (M.amin.y + M.amax.y),
+                    0.5f * (M.amin.z + M.amax.z));
+    const V3 e = v3(0.5f * (M.amax.x - M.amin.x), 0.5f * (M.amax.y - M.amin.y),
+                    0.5f * (M.amax.z - M.amin.z));
+    const float R = sqrtf(dot(e, e));
+    Rng r;
+    r.init(seed, (uint64_t)i);
+    V3 d = v3(0, 0, 1), x = v3(NAN, NAN, NAN);
+    int tries = 0;
+    int64_t steps = 0;
+    while (tries < 1000000) {
+        ++tries;
+        const float u0 = r.u(), u1 = r.u();
+        const float zc = 1.f - 2.f * u0, rr = sqrtf(fmaxf(0.f, 1.f - zc * zc));
+        float sp, cp;
+        sincosf(2.f * (float)M_PI * u1, &sp, &cp);
+        d = v3(rr * cp, rr * sp, zc);
+        V3 t1, t2;
+        basis(d, t1, t2);
+        const float rad = R * sqrtf(r.u());
+        sincosf(2.f * (float)M_PI * r.u(), &sp, &cp);
+        const V3 o = v3(c.x - R * d.x + rad * (cp * t1.x + sp * t2.x),
+                        c.y - R * d.y + rad * (cp * t1.y + sp * t2.y),
+                        c.z - R * d.z + rad * (cp * t1.z + sp * t2.z));
+        steps = 0;
+        if (delta_track(M, o, d, r, x, steps))
+            break;
+        x = v3(NAN, NAN, NAN);
+    }
+    const float u0 = r.u(), u1 = r.u();
+    const float zc = 1.f - 2.f * u0, rr = sqrtf(fmaxf(0.f, 1.f - zc * zc));
+    float sp, cp;
+    sincosf(2.f * (float)M_PI * u1, &sp, &cp);
+    pos[3 * i] = x.x;
+    pos[3 * i + 1] = x.y;
+    pos[3 * i + 2] = x.z;
+    view[3 * i] = -d.x;
+    view[3 * i + 1] = -d.y;
+    view[3 * i + 2] = -d.z;
+    light[3 * i] = rr * cp;
+    light[3 * i + 1] = rr * sp;
+    light[3 * i + 2] = zc;
+    if (attempts)
+        attempts[i] = tries;
+}
+
+// Path-traced pixels: first collision along each camera ray, then albedo times the
+// in-scattered radiance there (direct by next-event estimation plus the indirect
+// path estimate for a directional light; all in-scattered environment light in mode 1).
+template <bool TAB, bool SET>
+__global__ void __launch_bounds__(kPaths) k_render_mc(Medium M, TracerParams tp, V3 wl,
+                                                      const float *ray_o, const float *ray_d,
+                                                      int64_t N, int spp, Split sp, uint64_t seed,
+                                                      double *partial)
+{
+    const int64_t group = blockIdx.x / sp.nblk;
+    const int blk = blockIdx.x % sp.nblk;
+    const int64_t px = group * (kPaths / sp.seg) + threadIdx.x / sp.seg;
+    const int s = blk * sp.seg + (threadIdx.x & (sp.seg - 1));
+    double e = 0.0;
+    V3 d;
+    if (px < N && s < spp && unit(ray_d + 3 * px, d)) {
+        const V3 o = v3(ray_o[3 * px], ray_o[3 * px + 1], ray_o[3 * px + 2]);
+        Rng r;
+        r.init(seed, ((uint64_t)px << 20) + (uint64_t)s);
+        V3 x;
+        int64_t steps = 0;
+        if (!delta_track(M, o, d, r, x, steps)) {
+            e = tp.light_mode == 1 ? tp.irradiance : 0.0;
+        } else {
+            const V3 w = neg(d);
+            if constexpr (SET) {
+                const float4 lw = tp.set_dw[set_pick(tp, r.bits24())];
+                const V3 lj = v3(lw.x, lw.y, lw.z);
+                const float direct = lw.w * phase_eval<TAB>(tp, true, -dot_direct(w, lj)) *
+                                     ratio_track(M, x, lj, r, steps);
+                e = (double)tp.albedo *
+                    (double)fmaf(direct, tp.irradiance,
+                                 li_path<TAB, true>(M, tp, x, w, wl, false, r));
+            } else if (tp.light_mode == 0) {
+                const float direct = phase_eval<TAB>(tp, true, -dot_direct(w, wl)) *
+                                     ratio_track(M, x, wl, r, steps);
+                e = (double)tp.albedo *
+                    (double)fmaf(direct, tp.irradiance,
+                                 li_path<TAB, false>(M, tp, x, w, wl, false, r));
+            } else {
+                e = (double)tp.albedo * (double)li_path<TAB, false>(M, tp, x, w, wl, true, r);
+            }
+        }
+    }
+    segment_sums(e, e * e, sp.seg, px < N, partial + 2 * ((size_t)px * sp.nblk + blk));
+}
+
+// One camera sample per ray for the network renderer: the delta-tracked first
+// collision, the view direction there, and the direct single scattering from the
+// directional light (next-event estimation, times the albedo).  Rays that escape
+// get hit = 0 and zero outputs.
+__global__ void __launch_bounds__(256) k_first_hits(Medium M, TracerParams tp, V3 wl,
+                                                    const float *ray_o, const float *ray_d,
+                                                    int64_t N, uint64_t seed, uint64_t sample,
+                                                    float *pos, float *view, float *direct,
+                                                    uint8_t *hit)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= N)
+        return;
+    V3 d;
+    bool h = false;
+    float dir = 0.f;
+    V3 x = v3(0, 0, 0);
+    if (unit(ray_d + 3 * i, d)) {
+        const V3 o = v3(ray_o[3 * i], ray_o[3 * i + 1], ray_o[3 * i + 2]);
+        Rng r;
+        r.init(seed, ((uint64_t)i << 20) + sample);
+        int64_t steps = 0;
+        h = delta_track(M, o, d, r, x, steps);
+        if (h)
+            dir = tp.albedo * phase_eval<true>(tp, true, dot_direct(d, wl)) * ratio_track(M, x, wl, r, steps) *
+                  tp.irradiance;
+    }
+    pos[3 * i] = x.x;
+    pos[3 * i + 1] = x.y;
+    pos[3 * i + 2] = x.z;
+    view[3 * i] = h ? -d.x : 0.f;
+    view[3 * i + 1] = h ? -d.y : 0.f;
+    view[3 * i + 2] = h ? -d.z : 0.f;
+    direct[i] = dir;
+    hit[i] = h ? 1 : 0;
+}
+
 // Active records of a launch's range: usable directions and, with a mask, the wanted bits.
 // The others get zero sums here.
 __global__ void __launch_bounds__(256) k_active(const float *view, const float *light,
@@ -856,15 +1143,8 @@ __global__ void __launch_bounds__(256) k_active(const float *view, const float *
         list[base + (int)__popcll(m & ((1ull << lane) - 1))] = r;
 }
 
-// Launch geometry of the per-record sums: a wave holds kPaths / seg records, each owning
-// seg consecutive lanes (seg a power of two); records with more than kPaths paths have
-// nblk partial sums (then seg = kPaths), which k_finish_sums adds in order.
-struct Split {
-    int seg, nblk;
-};
-
 // Sum and sum of squares in FP64 of each record's path values, in a fixed tree order, for
-// the list's slots slot0 .. slot0 + n - 1; then the queue is empty for the next launch.
+// the list's slots slot0 .. slot0 + n - 1; then the queues are empty for the next launch.
 __global__ void __launch_bounds__(kPaths) k_path_sums(const double *val, const int32_t *list,
                                                       const int32_t *n_list, uint32_t *head,
                                                       int64_t rec0, int slot0, int n, int spp,
@@ -898,8 +1178,8 @@ __global__ void __launch_bounds__(kPaths) k_path_sums(const double *val, const i
             out[1] = b[t];
         }
     }
-    if (blockIdx.x == 0 && t == 0)
-        *head = 0;
+    if (blockIdx.x == 0 && t < (int)kQueues)
+        head[t * kQueueStride] = 0;
 }
 
 // Bits of the occupied bricks (see Medium), one wave per brick: brick (i, j, k) holds the
@@ -1275,6 +1555,76 @@ ds_status reduce_records(hipStream_t s, const double *partial, int64_t P, int nb
     return DS_OK;
 }
 
+// ------------------------------------------------------------------ which walk
+// Teams pay for a window per flight, whatever its length; one thread per path pays for every
+// collision, and a wave for its longest path.  So short paths are walked one per thread, and the
+// more of them there are the longer they may be, as then nothing waits for the longest.  The
+// measure is the box in mean free paths of the majorant, s (64^3 and 256^3 clouds, teams' time
+// over one thread's for s = 4 / 8 / 16 / 32 / 60):
+//   albedo 0.999,   64 paths    1.18 0.67 0.47 0.29 0.17      64000      1.59 0.98 0.57 0.38 0.30
+//                  320000       2.25 1.69 1.03 0.66 0.48      3200000    3.01 2.18 1.38 0.79 0.52
+//   albedo 0.5,   1000          1.20 1.00 0.76 0.43 0.31      320000     2.57 2.07 1.33 0.89 0.62
+//   environment,  1000          1.32 1.01 0.76 0.67 0.54      320000     2.60 2.19 1.76 1.25 0.98
+//   one interaction, 1000       1.49 1.29 0.91 0.65 0.49      320000     4.41 4.14 3.19 2.33 1.74
+//   1 / 4 / 16 paths (s = 8)    1.48 1.20 0.92: three launches more
+// The lines below follow the sizes at which both take as long, in paths (6 up to 2^15, 8 at 2^16,
+// 16 at 3 10^5, 24 from 2 10^6 on), in interactions that a path may have (few: less to wait
+// for) and for an environment (no ratio tracking).
+double box_flights(const ds_cloud *c, double ext_scale)
+{
+    return (double)c->majorant * ext_scale * c->h0 * ((double)c->nx + c->ny + c->nz) / 3.0;
+}
+
+bool serial_paths(const ds_cloud *c, const TracerParams &tp, int64_t paths)
+{
+    const double n = (double)std::max<int64_t>(1, paths);
+    double depth = 1.0 / std::max(1e-6, 1.0 - (double)tp.albedo);
+    if (tp.max_interactions > 0)
+        depth = std::min(depth, (double)tp.max_interactions);
+    const bool env = tp.light_mode == 1, many = n > 32768.0, single = n < 4.0;
+    if (env && single && depth <= 32.0)  // some twenty steps: 17 us, against 27 at any s
+        return true;
+    const double shallow = 1.0 + 5.0 * pow(depth, -2.5);
+    double line = std::max(6.0 + 30.0 / n, std::min(24.0, 8.0 + 3.3 * (log2(n) - 16.0)));
+    line *= many || single ? shallow : std::min(1.5, shallow);
+    if (env)
+        line *= many ? 3.0 : 1.5;
+    return box_flights(c, tp.ext_scale) < line;
+}
+
+// A launch of one thread per path holds fewer than 2^32 threads, up to two per path.
+constexpr int64_t kMaxSerial = (int64_t)1 << 31;
+
+// First hits: one flight and one ratio estimate per ray.  From 2^18 rays on one thread per ray
+// wins where the cells are near (64^3, 9 MB: 960 x 540 camera rays 1.58 to 1.09 for s = 4 to
+// 130, 1024^2 2.7 to 2.1) or the flights short; teams win where every lookup waits for HBM
+// (256^3, 550 MB: 960 x 540 rays 1.49 0.90 0.65 0.56 for s = 4 16 40 80, 1920 x 1080 1.89 1.09
+// 0.86 0.77; 128^3 1.59 1.15 1.04 0.91 and 2.48 1.96 1.72 1.64) or with fewer rays (384^2: 0.3 to
+// 0.76 everywhere).
+bool serial_first_hits(const ds_cloud *c, const TracerParams &tp, int64_t rays)
+{
+    if (rays < (int64_t)1 << 18 || rays >= kMaxSerial)
+        return false;
+    const double r = (double)rays / (1 << 18);
+    const double near = (double)(1 << 27) / (32.0 * (c->nx + 2.0) * (c->ny + 2.0) * (c->nz + 2.0));
+    return box_flights(c, tp.ext_scale) < 4.0 + 8.0 * r * sqrt(r) * near;
+}
+
+// Record draws: tries of one flight each, most of them a miss in thin clouds.  One thread per
+// record where a try is a flight or two and there are records enough to hide the longest
+// series of tries, or none to share with (s = 1 / 2 / 4: 262144 records 1.62 1.38 1.05, 40000
+// 0.93 0.74 0.60, one 1.30 1.17 1.02, four at s = 4 0.92).
+bool serial_draws(const ds_cloud *c, int64_t n)
+{
+    return box_flights(c, 1.0) < 4.0 && (n < 3 || n >= 200000) && n < kMaxSerial;
+}
+
+unsigned grid_of(int64_t n, Split sp)
+{
+    const int64_t rpb = kPaths / sp.seg;
+    return (unsigned)(((n + rpb - 1) / rpb) * sp.nblk);
+}
+
 // Paths per launch: the per-path values of one launch take at most 8 bytes x this (or one
 // record's paths).  At 2e7 paths/s a launch of 2^23 paths lasts some 0.4 s, so that the
 // few milliseconds in which its longest paths run alone do not count.
@@ -1285,8 +1635,10 @@ int64_t launch_records(int64_t P, int64_t spp)
     return std::min<int64_t>(P, std::max<int64_t>(1, kLaunchPaths / spp));
 }
 
-// Scratch of the walker's launches: counters (active records, queue head), the list of
+// Scratch of the walker's launches: counters (active records, queue heads), the list of
 // active records, the path values.
+constexpr size_t kCounterBytes = 4 * kQueueStride * (1 + kQueues);
+
 struct PathScratch {
     int32_t *counters, *list;
     double *val;
@@ -1297,9 +1649,9 @@ PathScratch path_scratch(void *ws, int64_t P)
     char *b = static_cast<char *>(ws);
     PathScratch r;
     r.counters = reinterpret_cast<int32_t *>(b);
-    r.list = reinterpret_cast<int32_t *>(b + 256);
+    r.list = reinterpret_cast<int32_t *>(b + kCounterBytes);
     r.val = reinterpret_cast<double *>(
-        b + 256 + (4 * (size_t)std::min<int64_t>(P, kLaunchPaths) + 255) / 256 * 256);
+        b + kCounterBytes + (4 * (size_t)std::min<int64_t>(P, kLaunchPaths) + 255) / 256 * 256);
     return r;
 }
 
@@ -1322,6 +1674,7 @@ void walk(hipStream_t s, const Medium &M, const TracerParams &tp, PathArgs &A, i
     const int64_t blocks = std::min<int64_t>((paths + teams - 1) / teams,
                                              kComputeUnits * kWalkBlocks);
     const int64_t per = paths / (blocks * (kWalkThreads / 64) * 4);  // a quarter of a wave's share
+    A.queues = (uint32_t)std::max<int64_t>(1, std::min<int64_t>(kQueues, blocks / 16));
     A.grab = (int)std::max<int64_t>(A.head ? 1 : 64 / team, std::min<int64_t>(per, 16));
     if (few)
         k_paths<KIND, TAB, SET, DIRECT, kTeamFew><<<(unsigned)blocks, kWalkThreads, 0, s>>>(M, tp, A);
@@ -1356,14 +1709,14 @@ ds_status walk_records(hipStream_t s, const float *dir, const float *light, cons
     const int64_t per = launch_records(P, A.spp);  // records of a launch
     for (int64_t rec0 = 0; rec0 < P; rec0 += kLaunchPaths) {
         const int n = (int)std::min<int64_t>(kLaunchPaths, P - rec0);
-        ds_status st = tracer_zero(s, reinterpret_cast<double *>(r.counters), 1);
+        ds_status st = tracer_zero(s, reinterpret_cast<double *>(r.counters), kCounterBytes / 8);
         if (st)
             return st;
         k_active<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(dir, light, mask, mask_bits, rec0, n,
                                                              sp.nblk, partial, r.list, r.counters);
         A.list = r.list;
         A.n_list = r.counters;
-        A.head = reinterpret_cast<uint32_t *>(r.counters + 1);
+        A.head = reinterpret_cast<uint32_t *>(r.counters + kQueueStride);
         A.rec0 = rec0;
         A.val = r.val;
         for (int64_t slot0 = 0; slot0 < n; slot0 += per) {
@@ -1379,12 +1732,13 @@ ds_status walk_records(hipStream_t s, const float *dir, const float *light, cons
     return DS_OK;
 }
 
-// The specialisation of the walker a call needs: tabulated phase functions and L_s records,
-// tables and light sets (pixels).
+// The walk a call needs: one thread per path or teams, and of these the specialisation for
+// tabulated phase functions and L_s records, tables and light sets (pixels).  paths: those
+// expected to be walked.
 ds_status launch_trace_li(hipStream_t s, const ds_cloud *c, const TracerParams &tp,
                           const float *pos, const float *view, const float *light, int64_t P,
                           int s0, int spp, uint64_t seed, const uint8_t *mask, uint8_t mask_bits,
-                          double *partial, void *ws)
+                          int64_t paths, double *partial, void *ws)
 {
     PathArgs A = {};
     A.a = pos;
@@ -1395,6 +1749,15 @@ ds_status launch_trace_li(hipStream_t s, const ds_cloud *c, const TracerParams &
     A.seed = seed;
     const Medium M = medium(c, tp.ext_scale);
     const bool tab = tp.ph_n > 0 || tp.pf_n > 0, dir = tp.include_direct != 0;
+    if (P * spp < kMaxSerial && serial_paths(c, tp, paths)) {
+        const Split sp = split(spp);
+        auto k = tab ? (dir ? k_trace_li<true, true> : k_trace_li<true, false>)
+                     : (dir ? k_trace_li<false, true> : k_trace_li<false, false>);
+        k<<<grid_of(P, sp), kPaths, 0, s>>>(M, tp, pos, view, light, P, s0, spp, sp, seed, mask,
+                                            mask_bits, partial);
+        DS_HIP(hipGetLastError());
+        return DS_OK;
+    }
     auto k = tab ? (dir ? walk<kRecordPaths, true, false, true> : walk<kRecordPaths, true, false, false>)
                  : (dir ? walk<kRecordPaths, false, false, true>
                         : walk<kRecordPaths, false, false, false>);
@@ -1414,6 +1777,14 @@ ds_status launch_render_mc(hipStream_t s, const ds_cloud *c, const TracerParams 
     A.seed = seed;
     const Medium M = medium(c, tp.ext_scale);
     const bool tab = tp.ph_n > 0 || tp.pf_n > 0, set = tp.light_mode == kLightSetMode;
+    if (N * spp < kMaxSerial && serial_paths(c, tp, N * spp)) {
+        const Split sp = split(spp);
+        auto k = tab ? (set ? k_render_mc<true, true> : k_render_mc<true, false>)
+                     : (set ? k_render_mc<false, true> : k_render_mc<false, false>);
+        k<<<grid_of(N, sp), kPaths, 0, s>>>(M, tp, wl, ray_o, ray_d, N, spp, sp, seed, partial);
+        DS_HIP(hipGetLastError());
+        return DS_OK;
+    }
     auto k = tab ? (set ? walk<kPixelPaths, true, true, false> : walk<kPixelPaths, true, false, false>)
                  : (set ? walk<kPixelPaths, false, true, false>
                         : walk<kPixelPaths, false, false, false>);
@@ -1426,7 +1797,7 @@ ds_status launch_render_mc(hipStream_t s, const ds_cloud *c, const TracerParams 
 size_t tracer_ws(int64_t P, int spp)
 {
     const size_t vals = (size_t)launch_records(P, spp) * (size_t)spp;
-    return 512 + 4 * (size_t)std::min<int64_t>(P, kLaunchPaths) +
+    return kCounterBytes + 256 + 4 * (size_t)std::min<int64_t>(P, kLaunchPaths) +
            8 * std::max<size_t>(vals, (size_t)std::min<int64_t>(P * (int64_t)spp, kLaunchPaths));
 }
 
@@ -1437,8 +1808,9 @@ ds_status tracer_li(hipStream_t s, const ds_cloud *c, const TracerParams &tp, co
 {
     const int nblk = tracer_blocks(spp);
     DS_TRY_MEDIUM(s, c);
+    // of a masked call (a frame's points whose stencils leave the grid) few records are wanted
     ds_status st = launch_trace_li(s, c, tp, pos, view, light, P, 0, spp, seed, mask, mask_bits,
-                                   partial, partial + 2 * P * nblk);
+                                   mask ? P * spp / 16 : P * spp, partial, partial + 2 * P * nblk);
     if (st)
         return st;
     return reduce_records(s, partial, P, nblk, spp, mean, var);
@@ -1474,7 +1846,8 @@ ds_status tracer_li_adaptive(hipStream_t s, const ds_cloud *c, const TracerParam
         }
         ++r;
         ds_status st = launch_trace_li(s, c, tp, pos, view, light, P, n, kb * batch, seed, active, 1,
-                                       partial, partial + 2 * P * sp1.nblk * ahead);
+                                       live * kb * batch, partial,
+                                       partial + 2 * P * sp1.nblk * ahead);
         if (st)
             return st;
         unsigned long long h = 0;
@@ -1511,6 +1884,12 @@ ds_status tracer_records(hipStream_t s, const ds_cloud *c, int64_t N, uint64_t s
                          float *view, float *light, int32_t *attempts)
 {
     DS_TRY_MEDIUM(s, c);
+    if (serial_draws(c, N)) {
+        k_sample_records<<<(unsigned)((N + 255) / 256), 256, 0, s>>>(medium(c), N, seed, pos, view,
+                                                                     light, attempts);
+        DS_HIP(hipGetLastError());
+        return DS_OK;
+    }
     PathArgs A = {};
     A.spp = 1;
     A.seed = seed;
@@ -1548,6 +1927,13 @@ ds_status tracer_first_hits(hipStream_t s, const ds_cloud *c, const TracerParams
              "the light direction is not a usable vector");
     const V3 wl = v3(l[0], l[1], l[2]);
     DS_TRY_MEDIUM(s, c);
+    if (serial_first_hits(c, tp, N)) {
+        k_first_hits<<<(unsigned)((N + 255) / 256), 256, 0, s>>>(medium(c, tp.ext_scale), tp, wl,
+                                                                 ray_o, ray_d, N, seed, sample, pos,
+                                                                 view, direct, hit);
+        DS_HIP(hipGetLastError());
+        return DS_OK;
+    }
     PathArgs A = {};
     A.a = ray_o;
     A.b = ray_d;
