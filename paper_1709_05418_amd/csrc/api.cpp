@@ -345,8 +345,9 @@ ds_status forward_plain(ds_ctx *ctx, const ds_net *net, const float *z, int64_t 
 
 // Training workspace of a minibatch of B samples, in floats (both network kinds).  The
 // progressive network's: per block the outputs F1, O of its two layers and their
-// pre-activation gradients DH, DA, the same (HO, DY) per dense trailing layer, and per row
-// d loss / d pre and the squared loss.
+// pre-activation gradients DH, DA, the same (HO, DY) per dense trailing layer, per row
+// d loss / d pre and the squared loss, and the gradients of parts of many rows.  It does not
+// shrink as B grows, nor change with the precision: a captured step's workspace stays.
 size_t train_ws_floats(const ds_net *net, int B)
 {
     if (net->kind == 1) {
@@ -359,8 +360,8 @@ size_t train_ws_floats(const ds_net *net, int B)
         split = split > csum ? split : csum;
         return 2 * act + 2 * (size_t)B * net->W + 2 * (size_t)B + split;
     }
-    const size_t BW = (size_t)B * net->W;
-    return 4 * net->K * BW + 2 * (net->H - 1) * BW + 2 * (size_t)B;
+    const size_t BW = (size_t)B * net->W, S = (size_t)grad_splits(net->K, net->W, net->H, B);
+    return 4 * net->K * BW + 2 * (net->H - 1) * BW + 2 * (size_t)B + (S > 1 ? S * net->n_params : 0);
 }
 
 ds_status train_ws(ds_net *net, int B, ChainArgs &a)
@@ -391,6 +392,7 @@ ds_status train_ws(ds_net *net, int B, ChainArgs &a)
     a.DY = take(Hd * BW);
     a.dpre = take(B);
     a.sq = take(B);
+    a.part = p;
     return DS_OK;
 }
 

@@ -241,10 +241,17 @@ struct ChainArgs {
     float *F1, *O, *HO, *out, *pre, *sq, *dpre;
     const float *target;
     float *DA, *DH, *DY;
+    float *part;  // [grad_splits][chain_params]: weight gradients of parts of the rows
     unsigned *amax;
     int split_v, split_w, split_l;  // set by chain_forward: sums formed in two parts
 };
 size_t chain_pack_bytes(int K, int W, int H, bool bf16);
+// parameters of the progressive network
+inline int64_t chain_params(int K, int W, int H)
+{
+    const int64_t w2 = (int64_t)W * W;
+    return K * (226 * (int64_t)W + w2 + 2 * W) + (K - 1) * w2 + (H - 1) * (w2 + W) + W + 1;
+}
 ds_status chain_pack(hipStream_t s, const ds_net *net);  // both forms, from net->theta
 ds_status chain_forward(hipStream_t s, const ChainArgs &a, bool bf16);
 ds_status chain_backward(hipStream_t s, const ChainArgs &a, bool bf16);
@@ -277,6 +284,8 @@ ds_status colsum(hipStream_t s, const float *d, int ldd, int R, int C, float *db
 int colsum_scratch(int C);
 // every weight and bias gradient of the progressive network, canonical order, from the
 // activations and gradients of a forward and backward chain
+// parts of B rows whose weight gradients are formed apart
+int grad_splits(int K, int W, int H, int B);
 ds_status weight_grads(hipStream_t s, const ChainArgs &a, float *grad, bool bf16);
 ds_status loss_mean(hipStream_t s, const float *sq, int B, float *loss);
 ds_status loss_head(hipStream_t s, const float *pre, const float *t, int B, float *dpre, float *sq,

@@ -2,6 +2,8 @@
 // through the progressive residual blocks and trailing layers, Adam on the FP32
 // master parameters.  Every reduction over the batch runs in a fixed order, so a
 // step is bitwise reproducible.
+#include <algorithm>
+
 #include "internal.h"
 
 namespace ds {
@@ -449,12 +451,17 @@ __global__ void __launch_bounds__(256) k_gemm_bf16(StridedGemm g, int kc, float 
 // ---------------------------------------------------------------- weight gradients
 // All weight and bias gradients of the progressive network in one launch: every matrix's
 // gradient is dY^T X over the minibatch's rows (dY the layer's pre-activation gradients, X
-// its inputs), a workgroup per 64 x 64 tile, some 500 of them for the paper's network, so no
-// product needs splitting; the blocks of a matrix's first tile column also add up dY's
-// columns, in FP32, for the bias.  (29 products of 4 to 16 tiles each, launched one by one
-// with their split sums and column sums, took 0.9 ms of a 1024-row step.)  Sums over more
-// than kFlush rows are added in parts of kFlush, in order.
-constexpr int kFlush = 1024;
+// its inputs), a workgroup per 64 x 64 tile, some 500 of them for the paper's network; the
+// blocks of a matrix's first tile column also add up dY's columns, in FP32, for the bias.
+// (29 products of 4 to 16 tiles each, launched one by one with their split sums and column
+// sums, took 0.9 ms of a 1024-row step.)  Where the tiles leave compute units idle over many
+// rows, the rows are split over blockIdx.y (grad_splits) and k_grad_sum adds the splits'
+// gradients in order.  Running sums take 64 rows (FP32) or one k step of TK (BF16) each.
+struct GradRows {
+    float *out;      // the gradient, or [split][n_params]
+    int64_t stride;  // floats between splits
+    int rows;        // of a split: a multiple of TK
+};
 
 struct GradTile {
     StridedGemm g;
@@ -473,7 +480,6 @@ __device__ __forceinline__ GradTile grad_tile(const ChainArgs &a, float *grad, i
     auto b1 = [&](int k) { return block(k) + 226 * (int64_t)W + (k > 0 ? w2 : 0); };
     auto head = [&](int m) { return block(K) + m * (w2 + W); };
     GradTile t = {};
-    t.g.K = (int)a.M;
     t.g.M = W;
     t.g.sam = 1;
     t.g.sak = W;
@@ -546,18 +552,19 @@ __device__ __forceinline__ void bias_sum(float (*red)[4], int r, int q, float s,
         t.db[t.m0 + m] = ((red[m][0] + red[m][1]) + red[m][2]) + red[m][3];
 }
 
-__global__ void __launch_bounds__(256) k_grad_bf16(ChainArgs a, float *grad)
+__global__ void __launch_bounds__(256) k_grad_bf16(ChainArgs a, GradRows r)
 {
     __shared__ __attribute__((aligned(16))) __bf16 As[TM][TKP];  // [row][k]
     __shared__ __attribute__((aligned(16))) __bf16 Bt[TN][TKP];  // [col][k]
     __shared__ float red[64][4];
-    const GradTile t = grad_tile(a, grad, blockIdx.x);
+    const GradTile t = grad_tile(a, r.out + blockIdx.y * r.stride, blockIdx.x);
+    const int kbeg = blockIdx.y * r.rows, kend = min((int)a.M, kbeg + r.rows);
     const StridedGemm &g = t.g;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int g4 = lane >> 4, n16 = lane & 15;
     const int wr = (w >> 1) * 32, wc = (w & 1) * 32;
-    const Stage sa = stage_of(g.A, g.sam, g.sak, t.m0, g.M, 0, tid);
-    Stage sb = stage_of(g.B, g.sbn, g.sbk, t.n0, g.N, 0, tid);
+    const Stage sa = stage_of(g.A, g.sam, g.sak, t.m0, g.M, kbeg, tid);
+    Stage sb = stage_of(g.B, g.sbn, g.sbk, t.n0, g.N, kbeg, tid);
     if (t.n0 + (tid & 63) == g.N - 1)  // the operand's columns are never read along k
         sb.p += t.last;
     f4 acc[2][2], sum[2][2];
@@ -567,9 +574,9 @@ __global__ void __launch_bounds__(256) k_grad_bf16(ChainArgs a, float *grad)
         for (int j = 0; j < 2; ++j)
             acc[i][j] = sum[i][j] = f4{0.f, 0.f, 0.f, 0.f};
     float va[NE], vb[NE], bias = 0.f;
-    sa.load(0, g.K, va);
-    sb.load(0, g.K, vb);
-    for (int k0 = 0; k0 < g.K; k0 += TK) {
+    sa.load(kbeg, kend, va);
+    sb.load(kbeg, kend, vb);
+    for (int k0 = kbeg; k0 < kend; k0 += TK) {
         stage_store<false>(As, nullptr, sa, tid, va);
         stage_store<false>(Bt, nullptr, sb, tid, vb);
         if (t.db) {
@@ -580,9 +587,9 @@ __global__ void __launch_bounds__(256) k_grad_bf16(ChainArgs a, float *grad)
             bias += s;
         }
         __syncthreads();
-        if (k0 + TK < g.K) {
-            sa.load(k0 + TK, g.K, va);
-            sb.load(k0 + TK, g.K, vb);
+        if (k0 + TK < kend) {
+            sa.load(k0 + TK, kend, va);
+            sb.load(k0 + TK, kend, vb);
         }
 #pragma unroll
         for (int ks = 0; ks < TK; ks += 32) {
@@ -598,15 +605,13 @@ __global__ void __launch_bounds__(256) k_grad_bf16(ChainArgs a, float *grad)
                 for (int j = 0; j < 2; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[i], y[j], acc[i][j], 0, 0, 0);
         }
-        if ((k0 + TK) % kFlush == 0) {
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    sum[i][j] += acc[i][j];
-                    acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
-                }
-        }
+            for (int j = 0; j < 2; ++j) {
+                sum[i][j] += acc[i][j];
+                acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+            }
         __syncthreads();
     }
 #pragma unroll
@@ -617,24 +622,25 @@ __global__ void __launch_bounds__(256) k_grad_bf16(ChainArgs a, float *grad)
             for (int q = 0; q < 4; ++q) {
                 const int row = t.m0 + wr + 16 * i + 4 * g4 + q, col = t.n0 + wc + 16 * j + n16;
                 if (row < g.M && col < g.N)
-                    g.C[(int64_t)row * g.ldc + col] = sum[i][j][q] + acc[i][j][q];
+                    g.C[(int64_t)row * g.ldc + col] = sum[i][j][q];
             }
     if (t.db)
         bias_sum(red, sa.kc ? tid >> 2 : tid & 63, sa.kc ? tid & 3 : tid >> 6, bias, t);
 }
 
-__global__ void __launch_bounds__(256) k_grad_f32(ChainArgs a, float *grad)
+__global__ void __launch_bounds__(256) k_grad_f32(ChainArgs a, GradRows r)
 {
     __shared__ float As[BK][BM + 4];
     __shared__ float Bs[BK][BN + 4];
     __shared__ float red[64][4];
-    const GradTile t = grad_tile(a, grad, blockIdx.x);
+    const GradTile t = grad_tile(a, r.out + blockIdx.y * r.stride, blockIdx.x);
+    const int kbeg = blockIdx.y * r.rows, kend = min((int)a.M, kbeg + r.rows);
     const StridedGemm &g = t.g;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int wm = (w & 1) * 32, wn = (w >> 1) * 32;
     const int li = lane & 15, lk = lane >> 4;
-    const StageF sa = stage_f(g.A, g.sam, g.sak, t.m0, g.M, 0, tid);
-    StageF sb = stage_f(g.B, g.sbn, g.sbk, t.n0, g.N, 0, tid);
+    const StageF sa = stage_f(g.A, g.sam, g.sak, t.m0, g.M, kbeg, tid);
+    StageF sb = stage_f(g.B, g.sbn, g.sbk, t.n0, g.N, kbeg, tid);
     if (t.n0 + (tid & 63) == g.N - 1)
         sb.p += t.last;
     f4v acc[2][2], sum[2][2];
@@ -644,9 +650,9 @@ __global__ void __launch_bounds__(256) k_grad_f32(ChainArgs a, float *grad)
         for (int j = 0; j < 2; ++j)
             acc[i][j] = sum[i][j] = f4v{0.f, 0.f, 0.f, 0.f};
     float va[NF], vb[NF], bias = 0.f, part = 0.f;
-    sa.load(0, g.K, va);
-    sb.load(0, g.K, vb);
-    for (int k0 = 0; k0 < g.K; k0 += BK) {
+    sa.load(kbeg, kend, va);
+    sb.load(kbeg, kend, vb);
+    for (int k0 = kbeg; k0 < kend; k0 += BK) {
         sa.store(As, va);
         sb.store(Bs, vb);
         if (t.db) {
@@ -655,9 +661,9 @@ __global__ void __launch_bounds__(256) k_grad_f32(ChainArgs a, float *grad)
                 part += va[j];
         }
         __syncthreads();
-        if (k0 + BK < g.K) {
-            sa.load(k0 + BK, g.K, va);
-            sb.load(k0 + BK, g.K, vb);
+        if (k0 + BK < kend) {
+            sa.load(k0 + BK, kend, va);
+            sb.load(k0 + BK, kend, vb);
         }
 #pragma unroll
         for (int ks = 0; ks < BK; ks += 4) {
@@ -700,6 +706,30 @@ __global__ void __launch_bounds__(256) k_grad_f32(ChainArgs a, float *grad)
             }
     if (t.db)
         bias_sum(red, sa.row, sa.kc ? tid & 3 : tid >> 6, bias, t);
+}
+
+// grad = the sum of S splits' gradients, in order.
+__global__ void __launch_bounds__(256) k_grad_sum(const float *__restrict__ part, int S, int64_t n,
+                                                  float *__restrict__ grad)
+{
+    constexpr int U = 8;
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n)
+        return;
+    float v = 0.f;
+    int s = 0;
+    for (; s + U <= S; s += U) {
+        float x[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+            x[k] = part[(s + k) * n + i];
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+            v += x[k];
+    }
+    for (; s < S; ++s)
+        v += part[s * n + i];
+    grad[i] = v;
 }
 
 __global__ void __launch_bounds__(256) k_splitk_sum(const float *P, int S, StridedGemm g)
@@ -834,13 +864,33 @@ ds_status colsum(hipStream_t s, const float *d, int ldd, int R, int C, float *db
     return DS_OK;
 }
 
+// Parts of the rows: as many as bring 640 workgroups about, of at least one k step each.  Loss and
+// gradient in us with 1 / 2 / 4 / 8 / 16 / 32 / 64 parts, 65536 rows FP32: 6 tiles (1 x 16, one
+// trailing layer) 3341 1774 983 590 393 295 263, 38 tiles (6 x 64) 3873 2282 1495 1229 1054 1002
+// 1000, 134 tiles (8 x 128) 4743 3609 2860 2690 2530 2482 2495; 1024 rows BF16: 46 38 32 29 (8
+// tiles), 111 105 105 106 (134).  The paper's network has 500 tiles and gains nothing (1024 rows
+// BF16 178 184 186 190).
+int grad_splits(int K, int W, int H, int B)
+{
+    return std::max(1, std::min(std::min(640 / grad_tiles(K, W, H), 128), B / TK));
+}
+
 ds_status weight_grads(hipStream_t s, const ChainArgs &a, float *grad, bool bf16)
 {
-    const unsigned blocks = (unsigned)grad_tiles(a.K, a.W, a.H);
+    const unsigned tiles = (unsigned)grad_tiles(a.K, a.W, a.H);
+    const int S = grad_splits(a.K, a.W, a.H, (int)a.M);
+    const int64_t n = chain_params(a.K, a.W, a.H);
+    GradRows r;
+    r.out = S > 1 ? a.part : grad;
+    r.stride = n;
+    r.rows = (int)(((a.M + S - 1) / S + TK - 1) / TK * TK);
+    const dim3 grid(tiles, (unsigned)((a.M + r.rows - 1) / r.rows));
     if (bf16)
-        k_grad_bf16<<<blocks, 256, 0, s>>>(a, grad);
+        k_grad_bf16<<<grid, 256, 0, s>>>(a, r);
     else
-        k_grad_f32<<<blocks, 256, 0, s>>>(a, grad);
+        k_grad_f32<<<grid, 256, 0, s>>>(a, r);
+    if (S > 1)
+        k_grad_sum<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(a.part, (int)grid.y, n, grad);
     DS_HIP(hipGetLastError());
     return DS_OK;
 }
