@@ -456,7 +456,10 @@ __global__ void __launch_bounds__(256) k_gemm_bf16(StridedGemm g, int kc, float 
 // (29 products of 4 to 16 tiles each, launched one by one with their split sums and column
 // sums, took 0.9 ms of a 1024-row step.)  Where the tiles leave compute units idle over many
 // rows, the rows are split over blockIdx.y (grad_splits) and k_grad_sum adds the splits'
-// gradients in order.  Running sums take 64 rows (FP32) or one k step of TK (BF16) each.
+// gradients in order.  A split's sums over more than 64 rows (FP32) or kFlush (BF16) are added in
+// parts of so many, in order.
+constexpr int kFlush = 1024;
+
 struct GradRows {
     float *out;      // the gradient, or [split][n_params]
     int64_t stride;  // floats between splits
@@ -605,13 +608,15 @@ __global__ void __launch_bounds__(256) k_grad_bf16(ChainArgs a, GradRows r)
                 for (int j = 0; j < 2; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[i], y[j], acc[i][j], 0, 0, 0);
         }
+        if ((k0 - kbeg + TK) % kFlush == 0) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+            for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                sum[i][j] += acc[i][j];
-                acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
-            }
+                for (int j = 0; j < 2; ++j) {
+                    sum[i][j] += acc[i][j];
+                    acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+                }
+        }
         __syncthreads();
     }
 #pragma unroll
@@ -622,7 +627,7 @@ __global__ void __launch_bounds__(256) k_grad_bf16(ChainArgs a, GradRows r)
             for (int q = 0; q < 4; ++q) {
                 const int row = t.m0 + wr + 16 * i + 4 * g4 + q, col = t.n0 + wc + 16 * j + n16;
                 if (row < g.M && col < g.N)
-                    g.C[(int64_t)row * g.ldc + col] = sum[i][j][q];
+                    g.C[(int64_t)row * g.ldc + col] = sum[i][j][q] + acc[i][j][q];
             }
     if (t.db)
         bias_sum(red, sa.kc ? tid >> 2 : tid & 63, sa.kc ? tid & 3 : tid >> 6, bias, t);
