@@ -364,9 +364,15 @@ __device__ __forceinline__ Weights<BF> &one_of(Weights<false> &a, Weights<BF> &b
 
 // Forward of T x 16 rows; the BF16 form takes the W-wide layers' operands as pairs (X3).
 // FP32 with one tile of rows: 5 waves per SIMD are 96 registers, without a spill (7, two
-// workgroups on a compute unit, spill 46 registers: 50000 rows 3105 us, 500 rows 204 us).
-template <bool BF, int T>
-__global__ void __launch_bounds__(1024, !BF && T == 1 ? 5 : 4) k_chain_forward(ChainArgs a)
+// workgroups on a compute unit, spill 46 registers: 50000 rows 3105 us, 500 rows 204 us).  The
+// BF16 form's 16 waves leave it 128 registers and spill 14 (18 below 13 waves' worth of
+// descriptors at once); up to four waves have as many as they need.
+// S: the number of waves, which decides how a level's descriptors are loaded (see z_load).
+enum Waves { kUpTo4, kUpTo12, kFrom13 };
+template <bool BF, int T, Waves S>
+__global__ void __launch_bounds__(S == kUpTo4 ? 256 : 1024,
+                                  S == kUpTo4 ? (BF ? 2 : 4) : !BF && T == 1 ? 5 : 4)
+    k_chain_forward(ChainArgs a)
 {
     typedef Lds<BF> X;
     constexpr int kR = T * kRows;  // rows of the workgroup
@@ -398,8 +404,8 @@ __global__ void __launch_bounds__(1024, !BF && T == 1 ? 5 : 4) k_chain_forward(C
     const int xz = n * ldz + Form<BF>::E * g, xw = n * ldw + Form<BF>::E * g;
     const int ncw = chunks<BF>(W), ncz = chunks<BF>(nf);
 
-    for (int e = tid; e < kR * ldz + (BF ? 4 : 1) * lo; e += nt)
-        zb[e] = (X)0.f;
+    for (int e = tid; e < (kR * ldz + (BF ? 4 : 1) * lo) * (int)sizeof(X) / 16; e += nt)
+        reinterpret_cast<uint4 *>(smem)[e] = uint4{0u, 0u, 0u, 0u};
     for (int e = tid; e < nv * WP; e += nt) {
         const int v = e / WP, f = e - v * WP, k = v / 3;
         float x = 0.f;
@@ -410,10 +416,13 @@ __global__ void __launch_bounds__(1024, !BF && T == 1 ? 5 : 4) k_chain_forward(C
     }
     __syncthreads();
     // A level's descriptors: unit u holds columns 64 (u & 3) + lane of row u >> 2; a wave takes
-    // every waves-th unit, up to kZ of them in flight (fewer waves: one after another).
-    constexpr int kZ = 5 * T;
+    // every waves-th unit, kZ of them in flight at a time.  The first kZ are loaded a layer
+    // ahead: all of them with 13 waves or more.  With fewer, a wave loads the others where it
+    // stores them, and up to four waves take 16 at a time (one by one, each waiting for HBM, as
+    // at first: 65536 rows of 6 x 32 FP32 689 us, of 5 a time 385 us, of 16 209 us; 1 x 16
+    // 119, 69 and 48 us).
+    constexpr int kZ = S == kUpTo4 ? 16 : 5 * T;
     const int waves = nt >> 6;
-    const bool ahead = waves * kZ >= 4 * kR;
     X *const zl = zb + place<BF>(lane);
     float zr[kZ];
     // (past the last row, column or unit: the last one's, so that no load waits on a branch)
@@ -426,24 +435,27 @@ __global__ void __launch_bounds__(1024, !BF && T == 1 ? 5 : 4) k_chain_forward(C
         if (u < 4 * kR && lane < kStencil - 64 * (u & 3))
             zl[(u >> 2) * ldz + 64 * (u & 3)] = (X)v;
     };
-    auto z_load = [&](int k, uint32_t at) {
-        if (ahead) {
+    auto z_load = [&](int k, uint32_t at, int u0) {
 #pragma unroll
-            for (int q = 0; q < kZ; ++q)
-                zr[q] = z_at(wave + q * waves, k, at);
-        }
+        for (int q = 0; q < kZ; ++q)
+            zr[q] = z_at(u0 + q * waves, k, at);
+    };
+    auto z_puts = [&](int u0) {
+#pragma unroll
+        for (int q = 0; q < kZ; ++q)
+            z_put(u0 + q * waves, zr[q]);
     };
     auto z_store = [&](int k) {
-        if (ahead) {
-#pragma unroll
-            for (int q = 0; q < kZ; ++q)
-                z_put(wave + q * waves, zr[q]);
-        } else {
-            for (int u = wave; u < 4 * kR; u += waves)
-                z_put(u, z_at(u, k, lane));
+        z_puts(wave);
+        if (S == kFrom13)
+            return;
+#pragma unroll 1
+        for (int u0 = wave + kZ * waves; u0 < 4 * kR; u0 += kZ * waves) {
+            z_load(k, lane, u0);
+            z_puts(u0);
         }
     };
-    z_load(0, lane);
+    z_load(0, lane, wave);
     z_store(0);
     float gamma[T];
 #pragma unroll
@@ -481,7 +493,7 @@ __global__ void __launch_bounds__(1024, !BF && T == 1 ? 5 : 4) k_chain_forward(C
         if (!BF || k > 0)
             load(w, pk.w(pk.W2(k)) + tw, 0, ncw);
         if (k + 1 < K)
-            z_load(k + 1, zl_at);
+            z_load(k + 1, zl_at, wave);
         // first layer of the block: the gamma input, bias, ReLU
         {
             const f4 gw = *reinterpret_cast<const f4 *>(vl + 3 * k * WP + f);
@@ -700,13 +712,21 @@ ds_status chain_forward(hipStream_t s, const ChainArgs &args, bool bf16)
     a.split_w = a.split_v && a.W > 128;
     a.split_l = rows < 64 && a.W > 128 && 2 * a.M <= (int64_t)16 * 226 * a.W;
     const unsigned blocks = (unsigned)((a.M + kRows - 1) / kRows), threads = 64 * ((a.W + 15) / 16);
-    if (bf16)
-        k_chain_forward<true, 1><<<blocks, threads, forward_lds<true>(a.K, a.W, a.H, kRows), s>>>(a);
-    else if (a.M <= kFewRows)
-        k_chain_forward<false, 1><<<blocks, threads, forward_lds<false>(a.K, a.W, a.H, kRows), s>>>(a);
-    else
-        k_chain_forward<false, 2>
-            <<<(blocks + 1) / 2, threads, forward_lds<false>(a.K, a.W, a.H, 2 * kRows), s>>>(a);
+    // Up to four waves take 16 rows however many there are: a second tile lengthens each wave's
+    // loads (65536 rows of 6 x 32 209 us with one, 323 with two; of 6 x 64 271 and 271).
+    const Waves S = threads <= 256 ? kUpTo4 : threads <= 768 ? kUpTo12 : kFrom13;
+    const int tiles = !bf16 && S != kUpTo4 && a.M > kFewRows ? 2 : 1;
+    const auto k =
+        S == kUpTo4    ? (bf16 ? k_chain_forward<true, 1, kUpTo4> : k_chain_forward<false, 1, kUpTo4>)
+        : S == kUpTo12 ? (bf16         ? k_chain_forward<true, 1, kUpTo12>
+                          : tiles == 1 ? k_chain_forward<false, 1, kUpTo12>
+                                       : k_chain_forward<false, 2, kUpTo12>)
+                       : (bf16         ? k_chain_forward<true, 1, kFrom13>
+                          : tiles == 1 ? k_chain_forward<false, 1, kFrom13>
+                                       : k_chain_forward<false, 2, kFrom13>);
+    k<<<(blocks + tiles - 1) / tiles, threads,
+        bf16 ? forward_lds<true>(a.K, a.W, a.H, kRows) : forward_lds<false>(a.K, a.W, a.H, tiles * kRows),
+        s>>>(a);
     DS_HIP(hipGetLastError());
     return DS_OK;
 }
