@@ -52,7 +52,7 @@ typedef int32_t ds_status;
 typedef enum { DS_F32 = 0, DS_BF16 = 1 } ds_dtype;
 
 /* Arithmetic of the network layers (Sec. 4.3).  DS_PREC_F32: plain form, every layer
- * in FP32 (descriptor materialised, one kernel per layer).  DS_PREC_BF16: fused
+ * in FP32 (descriptor materialised, then all layers in one kernel).  DS_PREC_BF16: fused
  * kernel, every layer's inputs and weights in BF16 on the matrix cores.  DS_PREC_FP8:
  * fused kernel with the W x W layers (W1, W2 of every block and the dense trailing
  * layers) in FP8 E4M3 (OCP) with power-of-two per-layer scales and the descriptor
@@ -205,8 +205,8 @@ ds_status ds_predict(ds_ctx *ctx, const ds_cloud *cloud, const ds_net *net,
 /* Builds ahead of time what ds_predict on (ctx, cloud, net, precision) with at most P
  * points would otherwise create on first use: for DS_PREC_F32 the cloud's float32
  * corner-packed levels and the context workspace of min(P, 65536) points (about
- * 4 (225 K + 1 + 3 W) + 1 bytes per point); nothing for the fused forms.  Synchronises
- * the stream.  Later ds_predict calls within those bounds allocate nothing and can be
+ * 4 (225 K + 1) + 1 bytes per point, an all-at-once MLP 4 (225 K + 1 + 3 W) + 1); nothing
+ * for the fused forms.  Synchronises the stream.  Later ds_predict calls within those bounds allocate nothing and can be
  * captured in a stream graph.  Errors as ds_predict, DS_ERR_OOM if memory runs out. */
 ds_status ds_predict_reserve(ds_ctx *ctx, const ds_cloud *cloud, const ds_net *net,
                              ds_precision precision, int64_t P);
@@ -214,9 +214,10 @@ ds_status ds_predict_reserve(ds_ctx *ctx, const ds_cloud *cloud, const ds_net *n
  * serving loops, harnesses that forbid hipMalloc): ds_predict in DS_PREC_F32 with the
  * same results, whose descriptor rows, activations and flags live in a scratch area
  * the library holds on every GPU from module load until the process ends (32 MiB per
- * device; chunks of up to floor((32 MiB - 256) / (4 (225 K + 1 + 3 W) + 1) / 64) * 64
- * points, 2880 at K = 10, W = 200).  It calls no hipMalloc, hipFree or other allocating
- * routine and never synchronises.  Arguments as ds_predict.  Errors: as ds_predict;
+ * device; chunks of up to floor((32 MiB - 256) / b / 64) * 64 points, b = 4 (225 K + 1) + 1
+ * bytes or, for an all-at-once MLP, 4 (225 K + 1 + 3 W) + 1: 3712 points at K = 10, an MLP of
+ * W = 200 2880).  It calls no hipMalloc, hipFree or other allocating routine and never
+ * synchronises.  Arguments as ds_predict.  Errors: as ds_predict;
  * DS_ERR_STATE if the cloud's float32 corner cells do not exist yet (run
  * ds_predict_reserve with DS_PREC_F32 once) or the device has no scratch address;
  * DS_ERR_INVALID_ARG if the network needs more than the scratch for 64 points.  All

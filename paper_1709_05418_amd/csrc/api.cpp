@@ -290,13 +290,21 @@ ds_status gather_cells(ds_ctx *ctx, const ds_cloud *c)
 
 constexpr int64_t kChunk = 65536;  // points per plain-form chunk
 
+// Floats of activations per row that a prediction in FP32 keeps (forward_plain).
+static size_t act_floats(const ds_net *net)
+{
+    return net->kind == 1 ? 3 * (size_t)net->W : 0;
+}
+
 // All-at-once MLP over `rows` descriptor rows in FP32: per layer one GEMM and a
-// bias + ReLU epilogue, ping-ponging between O and F (rows x W each); the scalar
+// bias + ReLU epilogue, ping-ponging between O and F (chunk x W each, at act); the scalar
 // output layer's pre-activation goes to pre (or T).
 static ds_status mlp_forward(ds_ctx *ctx, const ds_net *net, const float *z, int64_t rows,
-                             float *out, float *pre, float *O, float *F, float *T)
+                             float *out, float *pre, float *act)
 {
     hipStream_t s = ctx->stream;
+    const int64_t chunk = rows < kChunk ? rows : kChunk;
+    float *O = act, *F = O + chunk * net->W, *T = F + chunk * net->W;
     const std::vector<int> &wd = net->mlp_widths;
     const int L = (int)wd.size() - 1, D = wd[0];
     for (int64_t r0 = 0; r0 < rows; r0 += kChunk) {
@@ -311,8 +319,7 @@ static ds_status mlp_forward(ds_ctx *ctx, const ds_net *net, const float *z, int
             const bool last = l == L - 1;
             float *C = last ? (pre ? pre + r0 : T) : (l & 1 ? F : O);
             DS_TRY(gemm_strided(s, {M, no, ni, in, ld, 1, Wl, 1, ni, C, no, 0}));
-            DS_TRY(layer_epilogue(s, M, no, C, no, nullptr, 0, nullptr, 0, bl, nullptr, 0,
-                                  last ? out + r0 : C, no));
+            DS_TRY(layer_epilogue(s, M, no, C, bl, last ? out + r0 : C));
             in = C;
             ld = no;
         }
@@ -320,15 +327,16 @@ static ds_status mlp_forward(ds_ctx *ctx, const ds_net *net, const float *z, int
     return DS_OK;
 }
 
-// Plain FP32 network over `rows` descriptor rows (ldz = 225K + 1).
+// Plain FP32 network over `rows` descriptor rows (ldz = 225K + 1); act: act_floats() per row of
+// a chunk.
 // amax (may be NULL): running maxima of |activation| per layer, as float bits: the first
 // layer of every block (K), the residual stream over all blocks (1), the dense trailing
 // layers (H - 1).
 ds_status forward_plain(ds_ctx *ctx, const ds_net *net, const float *z, int64_t rows, float *out,
-                        float *pre, float *O, float *F, float *T, unsigned *amax = nullptr)
+                        float *pre, float *act, unsigned *amax = nullptr)
 {
     if (net->kind == 1)
-        return mlp_forward(ctx, net, z, rows, out, pre, O, F, T);
+        return mlp_forward(ctx, net, z, rows, out, pre, act);
     ChainArgs a = {};
     a.z = z;
     a.theta = net->theta;
@@ -452,8 +460,7 @@ static ds_status mlp_loss_grad(ds_net *net, const float *z, const float *target,
         // hidden-layer products with BF16 operand pairs, as the RPNN's W x W layers
         const StridedGemm gl = {B, no, ni, in, ld, 1, th + ow[l], 1, ni, A[l], no, 0};
         DS_TRY(bf && l > 0 ? gemm_bf16(s, gl, sp, split, true) : mm(gl));
-        DS_TRY(layer_epilogue(s, B, no, A[l], no, nullptr, 0, nullptr, 0, th + ob[l], nullptr, 0,
-                              Y[l], no));
+        DS_TRY(layer_epilogue(s, B, no, A[l], th + ob[l], Y[l]));
         in = Y[l];
         ld = no;
     }
@@ -522,7 +529,7 @@ ds_status loss_grad(ds_net *net, const float *z, const float *target, int B, flo
 using namespace ds;
 
 // ---------------------------------------------------------------- allocation-free plain form
-// Scratch of ds_predict_f32_noalloc: the descriptor rows, activations and flags of one
+// Scratch of ds_predict_f32_noalloc: the descriptor rows (an MLP's activations) and flags of one
 // chunk of points.  Every GPU the library runs on holds its own copy of this array from
 // module load until the process ends.  In host code its name is only a stand-in: kernels
 // get the device address that hipGetSymbolAddress gives for the current device, taken
@@ -1167,17 +1174,14 @@ ds_status ds_forward(ds_ctx *ctx, const ds_net *net, const float *z, int64_t P, 
         return DS_OK;
     DS_CHECK(z && out, DS_ERR_INVALID_ARG, "ds_forward: NULL device pointer");
     const int64_t rows = P < kChunk ? P : kChunk;
-    size_t need = sizeof(float) * (size_t)rows * net->W * 3;
-    ds_status st = ensure_ws(ctx, need);
+    ds_status st = ensure_ws(ctx, sizeof(float) * (size_t)rows * act_floats(net));
     if (st)
         return st;
-    float *O = static_cast<float *>(ctx->ws);
-    return forward_plain(ctx, net, z, P, out, pre_out, O, O + rows * net->W,
-                         O + 2 * rows * net->W);
+    return forward_plain(ctx, net, z, P, out, pre_out, static_cast<float *>(ctx->ws));
 }
 
-// The plain FP32 form in chunks of kChunk points: descriptor rows to HBM, then one GEMM
-// per layer (amax: see forward_plain).
+// The plain FP32 form in chunks of kChunk points: descriptor rows to HBM, then all layers in one
+// launch (the all-at-once MLP: one GEMM and one epilogue per layer; amax: see forward_plain).
 static ds_status predict_plain(ds_ctx *ctx, const ds_cloud *cloud, const ds_net *net,
                                const float *pos, const float *view_dir, const float *light_dir,
                                int64_t P, float *out, float *pre_out, uint8_t *flags,
@@ -1185,15 +1189,15 @@ static ds_status predict_plain(ds_ctx *ctx, const ds_cloud *cloud, const ds_net 
 {
     const int D = kStencil * net->K + 1;
     const int64_t rows = P < kChunk ? P : kChunk;
-    size_t need = sizeof(float) * (size_t)rows * ((size_t)D + 3 * net->W) + (size_t)rows;
+    size_t need = sizeof(float) * (size_t)rows * ((size_t)D + act_floats(net)) + (size_t)rows;
     ds_status st = ensure_ws(ctx, need);
     if (!st)
         st = gather_cells(ctx, cloud);
     if (st)
         return st;
     float *z = static_cast<float *>(ctx->ws);
-    float *O = z + rows * D;
-    uint8_t *fl_ws = reinterpret_cast<uint8_t *>(O + 3 * rows * net->W);
+    float *act = z + rows * D;
+    uint8_t *fl_ws = reinterpret_cast<uint8_t *>(act + rows * act_floats(net));
     GatherArgs a;
     gather_args(cloud, pos, view_dir, light_dir, P, a);
     for (int64_t p0 = 0; p0 < P; p0 += kChunk) {
@@ -1203,8 +1207,7 @@ static ds_status predict_plain(ds_ctx *ctx, const ds_cloud *cloud, const ds_net 
         st = gather_plain(ctx->stream, a, p0, np, DS_F32, z, D, fl);
         if (st)
             return st;
-        st = forward_plain(ctx, net, z, np, out + p0, pre_out ? pre_out + p0 : nullptr, O,
-                           O + rows * net->W, O + 2 * rows * net->W, amax);
+        st = forward_plain(ctx, net, z, np, out + p0, pre_out ? pre_out + p0 : nullptr, act, amax);
         if (st)
             return st;
         st = mask_invalid(ctx->stream, fl + p0, np, out + p0, pre_out ? pre_out + p0 : nullptr);
@@ -1230,7 +1233,7 @@ ds_status ds_predict_reserve(ds_ctx *ctx, const ds_cloud *cloud, const ds_net *n
     DS_HIP(hipSetDevice(ctx->device));
     const int64_t rows = P < kChunk ? P : kChunk;
     const size_t D = (size_t)kStencil * net->K + 1;
-    DS_TRY(ensure_ws(ctx, sizeof(float) * (size_t)rows * (D + 3 * (size_t)net->W) + (size_t)rows));
+    DS_TRY(ensure_ws(ctx, sizeof(float) * (size_t)rows * (D + act_floats(net)) + (size_t)rows));
     DS_TRY(gather_cells(ctx, cloud));
     DS_HIP(hipStreamSynchronize(ctx->stream));
     return DS_OK;
@@ -1257,17 +1260,17 @@ ds_status ds_predict_f32_noalloc(ds_ctx *ctx, const ds_cloud *cloud, const ds_ne
     DS_CHECK(cloud->cells32, DS_ERR_STATE,
              "ds_predict_f32_noalloc: the cloud's float32 corner cells do not exist (building "
              "them allocates): call ds_predict_reserve with DS_PREC_F32 once first");
-    // a chunk: descriptor rows [rows][D], three activation buffers [rows][W], flags [rows]
+    // a chunk: descriptor rows [rows][D], an MLP's three activation buffers [rows][W], flags [rows]
     const int D = kStencil * net->K + 1;
-    const size_t per_point = sizeof(float) * ((size_t)D + 3 * (size_t)net->W) + 1;
+    const size_t per_point = sizeof(float) * ((size_t)D + act_floats(net)) + 1;
     const int64_t fit = (int64_t)((kScratchBytes - 256) / per_point) / 64 * 64;
     DS_CHECK(fit >= 64, DS_ERR_INVALID_ARG,
              "ds_predict_f32_noalloc: a point needs %zu bytes of scratch, %zu bytes hold fewer "
              "than 64 points", per_point, kScratchBytes);
     const int64_t rows = P < fit ? P : fit;
     float *z = static_cast<float *>(g_scratch[ctx->device]);
-    float *O = z + rows * D;
-    uint8_t *fl_ws = reinterpret_cast<uint8_t *>(O + 3 * rows * net->W);
+    float *act = z + rows * D;
+    uint8_t *fl_ws = reinterpret_cast<uint8_t *>(act + rows * act_floats(net));
     GatherArgs a;
     gather_args(cloud, pos, view_dir, light_dir, P, a);
     for (int64_t p0 = 0; p0 < P; p0 += rows) {
@@ -1275,8 +1278,7 @@ ds_status ds_predict_f32_noalloc(ds_ctx *ctx, const ds_cloud *cloud, const ds_ne
         uint8_t *fl = flags ? flags : fl_ws - p0;  // the gather writes absolute indices
         ds_status st = gather_plain(ctx->stream, a, p0, np, DS_F32, z, D, fl);
         if (!st)
-            st = forward_plain(ctx, net, z, np, out + p0, pre_out ? pre_out + p0 : nullptr, O,
-                               O + rows * net->W, O + 2 * rows * net->W);
+            st = forward_plain(ctx, net, z, np, out + p0, pre_out ? pre_out + p0 : nullptr, act);
         if (!st)
             st = mask_invalid(ctx->stream, fl + p0, np, out + p0, pre_out ? pre_out + p0 : nullptr);
         if (st)

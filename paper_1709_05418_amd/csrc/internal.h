@@ -275,9 +275,8 @@ ds_status gemm_strided(hipStream_t s, const StridedGemm &g, float *split_ws = nu
 ds_status gemm_bf16(hipStream_t s, const StridedGemm &g, float *split_ws, size_t ws_floats,
                     bool x3 = false);
 int splitk_count(const StridedGemm &g);
-ds_status layer_epilogue(hipStream_t s, int M, int N, float *pre, int ldp, const float *gv, int ldg,
-                         const float *gw, int ldgw, const float *bias, const float *R, int ldr,
-                         float *out, int ldo);
+// pre ([M][N]) += bias, out = relu(pre)
+ds_status layer_epilogue(hipStream_t s, int M, int N, float *pre, const float *bias, float *out);
 ds_status relu_mask(hipStream_t s, float *x, int ldx, const float *pre, int ldp, int R, int C);
 // column sums in a fixed order; scratch holds colsum_scratch(C) floats
 ds_status colsum(hipStream_t s, const float *d, int ldd, int R, int C, float *db, float *scratch);

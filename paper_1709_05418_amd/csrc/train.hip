@@ -751,25 +751,16 @@ __global__ void __launch_bounds__(256) k_splitk_sum(const float *P, int S, Strid
     }
 }
 
-// Forward epilogue of a layer whose GEMM part is already in pre:
-// pre += g[m] gw[n] + bias[n] + R[m][n]; out = relu(pre).
-__global__ void __launch_bounds__(256) k_epilogue(int M, int N, float *pre, int ldp,
-                                                  const float *gv, int ldg, const float *gw,
-                                                  int ldgw, const float *bias, const float *R,
-                                                  int ldr, float *out, int ldo)
+// Forward epilogue of a layer whose GEMM part is already in pre ([M][N]):
+// pre += bias[n]; out = relu(pre).
+__global__ void __launch_bounds__(256) k_epilogue(int M, int N, float *pre, const float *bias, float *out)
 {
     const int64_t n = (int64_t)M * N;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t m = i / N, c = i % N;
-        float v = pre[m * ldp + c];
-        if (gv)
-            v += gv[m * ldg] * gw[c * ldgw];
-        v += bias[c];
-        if (R)
-            v += R[m * ldr + c];
-        pre[m * ldp + c] = v;
-        out[m * ldo + c] = fmaxf(v, 0.f);
+        const float v = pre[i] + bias[i % N];
+        pre[i] = v;
+        out[i] = fmaxf(v, 0.f);
     }
 }
 
@@ -832,12 +823,9 @@ ds_status gemm_bf16(hipStream_t s, const StridedGemm &g, float *split_ws, size_t
     return DS_OK;
 }
 
-ds_status layer_epilogue(hipStream_t s, int M, int N, float *pre, int ldp, const float *gv, int ldg,
-                         const float *gw, int ldgw, const float *bias, const float *R, int ldr,
-                         float *out, int ldo)
+ds_status layer_epilogue(hipStream_t s, int M, int N, float *pre, const float *bias, float *out)
 {
-    k_epilogue<<<grid1((int64_t)M * N), 256, 0, s>>>(M, N, pre, ldp, gv, ldg, gw, ldgw, bias, R, ldr,
-                                                     out, ldo);
+    k_epilogue<<<grid1((int64_t)M * N), 256, 0, s>>>(M, N, pre, bias, out);
     DS_HIP(hipGetLastError());
     return DS_OK;
 }

@@ -188,3 +188,28 @@ def test_old_blocks_make_way_for_the_sizes_in_use(run):
     L.ds_destroy(ctx)
     assert F.fake_live_bytes() <= start
     """)
+
+
+def test_the_progressive_network_keeps_no_activations(run):
+    # its layers are chained in one launch; the all-at-once MLPs keep three activations a row
+    run("""
+    ctx = context()
+    net, mlp = C.c_void_p(), C.c_void_p()
+    assert L.ds_net_create(ctx, C.byref(ds._NetDesc(2, 64, 3)), C.byref(net)) == 0
+    assert L.ds_net_create_mlp(ctx, 2, 2, (C.c_int32 * 2)(64, 1), C.byref(mlp)) == 0
+    rows = 65536
+    at = free()
+    assert L.ds_forward(ctx, net, density, C.c_int64(rows), density, density) == 0
+    assert free() == at
+    c = cloud(ctx, 8)
+    assert L.ds_predict_reserve(ctx, c, net, 0, C.c_int64(64)) == 0   # the cloud's cells
+    at = free()
+    assert L.ds_predict_reserve(ctx, c, net, 0, C.c_int64(rows)) == 0
+    held = free()
+    assert abs(held - at - (rows - 64) * (4 * 451 + 1)) < 8192
+    assert L.ds_predict(ctx, c, net, 0, density, density, density, C.c_int64(100000), density,
+                        None, None) == 0
+    assert free() == held
+    assert L.ds_predict_reserve(ctx, c, mlp, 0, C.c_int64(rows)) == 0
+    assert abs(free() - at - (rows - 64) * 4 * 451 - rows * 4 * 192) < 1 << 20
+    """)
