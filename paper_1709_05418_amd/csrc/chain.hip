@@ -704,13 +704,16 @@ ds_status chain_forward(hipStream_t s, const ChainArgs &args, bool bf16)
     ChainArgs a = args;
     if (a.M <= 0)
         return DS_OK;
-    // The BF16 sums of fewer than 64 tiles of 64 x 64 outputs are formed in two parts, inputs
-    // below 128 and from there on (within a bound on the parts' size): the order such
-    // products had as launches of their own, split to fill the chip.
+    // Small batches form their BF16 sums over more than 128 inputs in two parts, the first 128
+    // inputs and the rest: batches of at most 1808 rows whose W-wide outputs make fewer than 64
+    // tiles of 64 x 64 (W = 200: 960 rows, W <= 64: 1808), for the scalar layer up to 4032 rows.
+    // One sum would do as well, but the two round apart, and a ReLU whose argument is a rounding
+    // error then changes sides: the lines lie where they have always been, so that a training
+    // run repeats.
     const int64_t rows = (a.M + 63) / 64, cols = (a.W + 63) / 64;
-    a.split_v = rows * cols < 64 && 2 * a.M <= 16 * 226;
+    a.split_v = rows * cols < 64 && a.M <= 1808;
     a.split_w = a.split_v && a.W > 128;
-    a.split_l = rows < 64 && a.W > 128 && 2 * a.M <= (int64_t)16 * 226 * a.W;
+    a.split_l = rows < 64 && a.W > 128;
     const unsigned blocks = (unsigned)((a.M + kRows - 1) / kRows), threads = 64 * ((a.W + 15) / 16);
     // Up to four waves take 16 rows however many there are: a second tile lengthens each wave's
     // loads (65536 rows of 6 x 32 209 us with one, 323 with two; of 6 x 64 271 and 271).
