@@ -999,19 +999,19 @@ ds_status ds_net_create(ds_ctx *ctx, const ds_net_desc *desc, ds_net **out)
     n->W = desc->W;
     n->H = desc->H;
     n->n_params = ds_net_param_count(desc);
-    const size_t cb = chain_pack_bytes(n->K, n->W, n->H, false);
-    const size_t cb16 = chain_pack_bytes(n->K, n->W, n->H, true);
-    if (device_malloc(&n->theta, sizeof(float) * n->n_params) != hipSuccess ||
-        device_malloc(&n->chain, cb) != hipSuccess || device_malloc(&n->chain16, cb16) != hipSuccess) {
+    // one allocation: the parameters, then both packed copies
+    auto up = [](size_t bytes) { return (bytes + 255) / 256 * 256; };
+    const size_t tb = up(sizeof(float) * n->n_params);
+    const size_t cb = up(chain_pack_bytes(n->K, n->W, n->H, false));
+    const size_t all = tb + cb + chain_pack_bytes(n->K, n->W, n->H, true);
+    if (device_malloc(&n->theta, all) != hipSuccess) {
         ds_net_destroy(n);
         set_error("ds_net_create: out of device memory");
         return DS_ERR_OOM;
     }
-    hipError_t e = hipMemsetAsync(n->theta, 0, sizeof(float) * n->n_params, ctx->stream);
-    if (e == hipSuccess)
-        e = hipMemsetAsync(n->chain, 0, cb, ctx->stream);
-    if (e == hipSuccess)
-        e = hipMemsetAsync(n->chain16, 0, cb16, ctx->stream);
+    n->chain = reinterpret_cast<char *>(n->theta) + tb;
+    n->chain16 = reinterpret_cast<char *>(n->theta) + tb + cb;
+    hipError_t e = hipMemsetAsync(n->theta, 0, all, ctx->stream);
     if (e != hipSuccess) {
         ds_net_destroy(n);
         return hip_fail(e, "ds_net_create");
@@ -1119,8 +1119,6 @@ ds_status ds_net_destroy(ds_net *net)
     (void)hipFree(net->vec);
     (void)hipFree(net->fmap);
     (void)hipFree(net->vmap);
-    (void)hipFree(net->chain);
-    (void)hipFree(net->chain16);
     (void)hipFree(net->frag_fp8);
     (void)hipFree(net->vec8);
     (void)hipFree(net->tws);

@@ -126,7 +126,7 @@ struct ds_net {
     std::vector<int32_t> fp8_exps;  // log2 units of the activations, then matrix exponents
     bool fp8_ready = false;       // FP8 form matches the current parameters
     // the matrices in the layer chains' fragment order, FP32 and BF16 (chain.hip); like the
-    // fragments above they follow every change of theta
+    // fragments above they follow every change of theta, in whose allocation they lie
     void *chain = nullptr, *chain16 = nullptr;
     // training workspace (activations and gradients of one minibatch)
     float *tws = nullptr;
