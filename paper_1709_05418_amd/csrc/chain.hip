@@ -10,9 +10,10 @@
 // products per 16 rows, 67 us at 157 TFLOP/s over 256 compute units).  Per workgroup the
 // 1.3 M parameters of the paper's network pass through a compute unit's vector memory path
 // once (5.2 MB, 35 us at 64 B per clock).  K = 10, W = 200, H = 3: 500 rows forward FP32
-// 160 us, backward 101 us, 1024 rows BF16 95 and 42 us; loss and gradient of 500 rows
-// 1482 us as one GEMM (9 to 13 us) or two and an epilogue per layer, 299 us so; a training
-// step of 1024 rows 1364 and 258 us; 50000 rows' forward 2550 and 1873 us.
+// 158 us, backward 101 us, 1024 rows BF16 88 and 42 us; loss and gradient of 500 rows
+// 1482 us as one GEMM (9 to 13 us) or two and an epilogue per layer, 297 us so; a training
+// step of 1024 rows 1364 and 248 us; 50000 rows' forward 2550 and 1853 us (the FP32 matrix
+// cores busy for 48 % of it).
 #include <algorithm>
 
 #include "internal.h"
