@@ -418,13 +418,10 @@ __global__ void __launch_bounds__(kWalkThreads, kWalkBlocks) k_paths(Medium M, T
 
     const int lane = threadIdx.x & 63, i = lane & (TEAM - 1), lead = lane & ~(TEAM - 1);
     const uint32_t waves = gridDim.x * (kWalkThreads / 64);
-    // the wave's items: q0 .. q1 - 1; the queue it takes from
-    uint32_t share = (blockIdx.x * (kWalkThreads / 64) + (threadIdx.x >> 6)) * (uint32_t)A.grab;
-    uint32_t q0 = 0, q1 = 0, queue = blockIdx.x % A.queues;
-    bool more = true;
+    // the wave's items: q0 .. q1 - 1; the queue it takes from (kQueues: all are empty)
     constexpr bool kQueued = KIND == kRecordPaths || KIND == kPixelPaths;
-    const uint32_t per = kQueued ? (total + A.queues - 1) / A.queues : 0;  // items of a queue
-    auto items_of = [&](uint32_t k) { return k * per < total ? min(per, total - k * per) : 0; };
+    uint32_t share = (blockIdx.x * (kWalkThreads / 64) + (threadIdx.x >> 6)) * (uint32_t)A.grab;
+    uint32_t q0 = 0, q1 = 0, queue = kQueued ? blockIdx.x % A.queues : 0;
 
     int phase = kNew, j = 0, steps = 0;
     WordPos<KIND> q = 0;
@@ -507,8 +504,15 @@ __global__ void __launch_bounds__(kWalkThreads, kWalkBlocks) k_paths(Medium M, T
             if (n > have) {
                 const uint32_t take = max((uint32_t)A.grab, n - have);
                 uint32_t base = 0, avail = 0;
-                while (more && avail == 0) {
-                    if constexpr (kQueued) {
+                if constexpr (kQueued) {
+                    // items of a queue, formed anew here: kept over the walk, it costs registers
+                    uint32_t queues = A.queues;
+                    asm volatile("" : "+s"(queues));
+                    const uint32_t per = (total + queues - 1) / queues;
+                    auto items_of = [&](uint32_t k) {
+                        return k * per < total ? min(per, total - k * per) : 0;
+                    };
+                    while (queue < kQueues && avail == 0) {
                         if (lane == 0)
                             base = atomicAdd(A.head + queue * kQueueStride, take);
                         base = __builtin_amdgcn_readfirstlane(base);
@@ -516,33 +520,35 @@ __global__ void __launch_bounds__(kWalkThreads, kWalkBlocks) k_paths(Medium M, T
                         avail = base < len ? min(take, len - base) : 0;
                         base += queue * per;
                         if (avail == 0) {  // on to the next queue that is not empty
-                            const uint32_t l = min((uint32_t)lane, A.queues - 1);
+                            const uint32_t l = min((uint32_t)lane, queues - 1);
                             const uint64_t open = __ballot(
                                 __hip_atomic_load(A.head + l * kQueueStride, __ATOMIC_RELAXED,
                                                   __HIP_MEMORY_SCOPE_AGENT) < items_of(l));
                             const uint64_t after = open & (~0ull << queue);
-                            more = open != 0;
-                            queue = more ? __builtin_ctzll(after ? after : open) : 0;
+                            queue = open ? __builtin_ctzll(after ? after : open) % queues : kQueues;
                         }
-                    } else {
-                        base = share;
-                        avail = base < total ? min(take, total - base) : 0;
-                        share += waves * (uint32_t)A.grab;
-                        more = avail != 0;
                     }
-                }
-                if (rank >= have && rank - have < avail) {
-                    next = base + (rank - have);
-                    got = true;
+                    if (rank >= have && rank - have < avail) {
+                        next = base + (rank - have);
+                        got = true;
+                    }
+                } else {
+                    base = share;
+                    avail = take;
+                    share += waves * (uint32_t)A.grab;
+                    if (rank >= have)
+                        next = base + (rank - have);
                 }
                 q0 = base + min(n - have, avail);
                 q1 = base + avail;
             } else {
                 q0 += n;
             }
+            if constexpr (!kQueued)
+                got = next < total;
             if (phase == kNew) {
                 if (!got) {
-                    if (!more)
+                    if (!kQueued || queue >= kQueues)
                         phase = kDone;
                 } else {
                     item = next;
