@@ -71,9 +71,10 @@ void blocks_free(ds_ctx *ctx)
     r.erase(std::remove_if(r.begin(), r.end(), freed), r.end());
 }
 
-// The process's contexts, whose kept blocks an allocation may need.
+// The process's contexts, whose kept blocks an allocation may need.  Never destroyed: a context
+// may be closed while the process ends.
 static std::mutex g_contexts_mutex;
-static std::vector<ds_ctx *> g_contexts;
+static std::vector<ds_ctx *> &g_contexts = *new std::vector<ds_ctx *>;
 
 static bool context_add(ds_ctx *ctx)
 {
